@@ -578,54 +578,146 @@ struct FinalParams {
   int n_dist;
   int K[kMaxDist];
   int off[kMaxDist + 1];
+  int tile_off[kMaxDist + 1];  // first workgroup of each distribution
   int entries;
   int n_sub;
+  int group;  // sub-ensembles per sweep over the terms, at most kFinSubs
   double inv_ns;
 };
 
-// One workgroup per output point; threads split the frequency sum, and the
-// sub-ensemble estimates are folded with Welford's update.
-__global__ __launch_bounds__(256) void counts_finalize(FinalParams p, const double* __restrict__ acc,
-                                                       double* __restrict__ P_re,
-                                                       double* __restrict__ P_im,
-                                                       double* __restrict__ sigma) {
-  __shared__ double red_r[256], red_i[256];
-  const int e = blockIdx.x;
+// Inverse DFT of every sub-ensemble and the statistics over them.  A
+// workgroup owns kFinL output points of one distribution.  It walks the terms
+// kFinThreads at a time: each thread loads one term of `group` sub-ensembles
+// (coalesced), the terms that are zero in all of them (the grid points the
+// counting kernels skip: at M = 8000 all but a few hundred of 4160) are
+// dropped by a ballot prefix sum, and the rest go to LDS with their index.
+// The threads, kFinL points by kFinPhases phases of that list, then form each
+// twiddle e^{-2 pi i (t l mod K) / K} once for the group from two tables (64
+// and K / 64 entries; one product, two roundings) and add 4 FMAs per term and
+// sub-ensemble.  Bound by those FMAs on dense accumulators and by the loads
+// (every workgroup reads all terms, from L2) on sparse ones.  kFinL = 16: 260
+// workgroups at K = 4160, two per CU.  One output point per workgroup with one
+// sincospi per term and sub-ensemble took 1837 us for windows of 4 x 2176 and
+// 4352 points and 15 sub-ensembles and 476 us for 4160 points and 8 (now 87
+// and 28 us).
+constexpr int kFinL = 16, kFinPhases = 32, kFinSubs = 6, kFinThreads = kFinL * kFinPhases;
+constexpr int kFinMaxK = 65536;
+
+__global__ __launch_bounds__(kFinThreads) void counts_finalize(FinalParams p,
+                                                               const double* __restrict__ acc,
+                                                               double* __restrict__ P_re,
+                                                               double* __restrict__ P_im,
+                                                               double* __restrict__ sigma) {
+  typedef __attribute__((ext_vector_type(2), aligned(8))) double d2u;  // acc: any FP64 address
+  typedef __attribute__((ext_vector_type(2))) double d2;
+  constexpr int kWaves = kFinThreads / 64;
+  __shared__ d2 tw_hi[kFinMaxK / 64 + 1], tw_lo[64];
+  __shared__ d2 xs[kFinThreads][kFinSubs];
+  __shared__ uint32_t ts[kFinThreads];
+  __shared__ d2 red[kWaves][kFinSubs][kFinL];
+  __shared__ int wcnt[kWaves];
   int q = 0;
-  while (q + 1 < p.n_dist && e >= p.off[q + 1]) ++q;
-  const int K1 = p.K[q], l1 = e - p.off[q], nterms = K1;
+  while (q + 1 < p.n_dist && (int)blockIdx.x >= p.tile_off[q + 1]) ++q;
+  const int K = p.K[q];
+  const int tid = threadIdx.x, li = tid & (kFinL - 1), phase = tid / kFinL;
+  const int wave = tid >> 6, lane = tid & 63;
+  const int lo = ((int)blockIdx.x - p.tile_off[q]) * kFinL + li;
+  const uint32_t l = (uint32_t)(lo < K ? lo : K - 1);
+  const float inv_k = 1.0f / (float)K;
+  for (int i = tid; i <= (K - 1) / 64; i += kFinThreads) {
+    double sw, cw;
+    sincospi(-2.0 * ((double)(64 * i) / K), &sw, &cw);
+    tw_hi[i] = d2{cw, sw};
+  }
+  if (tid < 64) {
+    double sw, cw;
+    sincospi(-2.0 * ((double)tid / K), &sw, &cw);
+    tw_lo[tid] = d2{cw, sw};
+  }
   double mean_r = 0.0, mean_i = 0.0, m2 = 0.0;
-  for (int s = 0; s < p.n_sub; ++s) {
-    const double* a = acc + ((int64_t)s * p.entries + p.off[q]) * 2;
-    double sr = 0.0, si = 0.0;
-    for (int t = threadIdx.x; t < nterms; t += 256) {
-      const double frac = (double)(((int64_t)t * l1) % K1) / K1;
-      double sw, cw;
-      sincospi(-2.0 * frac, &sw, &cw);
-      const double xr = a[2 * t], xi = a[2 * t + 1];
-      sr += xr * cw - xi * sw;
-      si += xr * sw + xi * cw;
-    }
-    red_r[threadIdx.x] = sr;
-    red_i[threadIdx.x] = si;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-      if (threadIdx.x < w) {
-        red_r[threadIdx.x] += red_r[threadIdx.x + w];
-        red_i[threadIdx.x] += red_i[threadIdx.x + w];
+  for (int s0 = 0; s0 < p.n_sub; s0 += p.group) {
+    const int sc = p.n_sub - s0 < p.group ? p.n_sub - s0 : p.group;
+    const d2u* a = (const d2u*)acc + (int64_t)s0 * p.entries + p.off[q];
+    double ar[kFinSubs], ai[kFinSubs];
+#pragma unroll
+    for (int u = 0; u < kFinSubs; ++u) ar[u] = ai[u] = 0.0;
+    for (int t0 = 0; t0 < K; t0 += kFinThreads) {
+      const int t = t0 + tid;
+      d2 x[kFinSubs];
+      bool nz = false;  // a NaN counts as nonzero
+#pragma unroll
+      for (int u = 0; u < kFinSubs; ++u) {
+        x[u] = d2{0.0, 0.0};
+        if (u < sc && t < K) x[u] = a[(int64_t)u * p.entries + t];
+        nz |= x[u].x != 0.0 || x[u].y != 0.0;
+      }
+      const unsigned long long mask = __ballot(nz);
+      __syncthreads();  // the previous terms are consumed
+      if (lane == 0) wcnt[wave] = __popcll(mask);
+      __syncthreads();
+      int base = 0, count = 0;
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) {
+        base += w < wave ? wcnt[w] : 0;
+        count += wcnt[w];
+      }
+      if (nz) {
+        const int at = base + __popcll(mask & ((1ull << lane) - 1ull));
+        ts[at] = (uint32_t)t;
+#pragma unroll
+        for (int u = 0; u < kFinSubs; ++u)
+          if (u < sc) xs[at][u] = x[u];
       }
       __syncthreads();
+      for (int i = phase; i < count; i += kFinPhases) {
+        // t l < 2^32 (K <= 65536); its quotient by K is below 65536 and its FP32
+        // estimate at most one off
+        const uint32_t tl = ts[i] * l;
+        int r = (int)(tl - (uint32_t)((float)tl * inv_k) * (uint32_t)K);
+        r += r < 0 ? K : 0;
+        r -= r >= K ? K : 0;
+        const d2 h = tw_hi[r >> 6], g = tw_lo[r & 63];
+        const double wr = fma(h.x, g.x, -(h.y * g.y)), wi = fma(h.x, g.y, h.y * g.x);
+#pragma unroll
+        for (int u = 0; u < kFinSubs; ++u)
+          if (u < sc) {
+            const d2 v = xs[i][u];
+            ar[u] = fma(v.x, wr, fma(-v.y, wi, ar[u]));
+            ai[u] = fma(v.x, wi, fma(v.y, wr, ai[u]));
+          }
+      }
     }
-    if (threadIdx.x == 0) {
-      const double ps_r = red_r[0] * p.inv_ns / nterms, ps_i = red_i[0] * p.inv_ns / nterms;
-      const double dr = ps_r - mean_r;
-      mean_r += dr / (s + 1);
-      mean_i += (ps_i - mean_i) / (s + 1);
-      m2 += dr * (ps_r - mean_r);
+    // the four phases of a wave, then the waves, in a fixed order
+#pragma unroll
+    for (int u = 0; u < kFinSubs; ++u) {
+      ar[u] += __shfl_xor(ar[u], 16, 64);
+      ai[u] += __shfl_xor(ai[u], 16, 64);
+      ar[u] += __shfl_xor(ar[u], 32, 64);
+      ai[u] += __shfl_xor(ai[u], 32, 64);
+      if (lane < kFinL) red[wave][u][li] = d2{ar[u], ai[u]};
+    }
+    __syncthreads();
+    if (tid < kFinSubs * kFinL) {
+      const int u = tid / kFinL;
+      d2 s = red[0][u][li];
+#pragma unroll 2
+      for (int w = 1; w < kWaves; ++w) s += red[w][u][li];
+      red[0][u][li] = d2{s.x * p.inv_ns / K, s.y * p.inv_ns / K};
+    }
+    __syncthreads();
+    if (tid < kFinL) {  // Welford's update over the sub-ensembles
+      for (int u = 0; u < sc; ++u) {
+        const d2 v = red[0][u][li];
+        const double dr = v.x - mean_r;
+        mean_r += dr / (s0 + u + 1);
+        mean_i += (v.y - mean_i) / (s0 + u + 1);
+        m2 += dr * (v.x - mean_r);
+      }
     }
     __syncthreads();
   }
-  if (threadIdx.x == 0) {
+  if (tid < kFinL && lo < K) {
+    const int e = p.off[q] + lo;
     P_re[e] = mean_r;
     if (P_im) P_im[e] = mean_i;
     sigma[e] = p.n_sub > 1 ? sqrt(m2 / (p.n_sub - 1) / p.n_sub) : __builtin_nan("");
@@ -1057,12 +1149,16 @@ mp_status counts_finalize_launch(int32_t d, mp_bin_mode mode, const int32_t* K, 
   for (int q = 0; q < p.n_dist; ++q) {
     p.K[q] = K[q];
     p.off[q + 1] = p.off[q] + K[q];
+    p.tile_off[q + 1] = p.tile_off[q] + (K[q] + kFinL - 1) / kFinL;
   }
   p.entries = (int)entries_of(d, mode, K);
   p.n_sub = n_sub;
   p.inv_ns = 1.0 / (double)ns;
-  hipLaunchKernelGGL(counts_finalize, dim3(p.entries), dim3(256), 0, stream, p, acc, P_re, P_im,
-                     sigma);
+  // equal groups of at most kFinSubs sub-ensembles
+  const int groups = (n_sub + kFinSubs - 1) / kFinSubs;
+  p.group = (n_sub + groups - 1) / groups;
+  hipLaunchKernelGGL(counts_finalize, dim3(p.tile_off[p.n_dist]), dim3(kFinThreads), 0, stream, p,
+                     acc, P_re, P_im, sigma);
   MP_HIP_LAUNCH_CHECK("mp_counts_finalize launch");
   return MP_OK;
 }
