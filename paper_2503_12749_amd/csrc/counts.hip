@@ -725,7 +725,7 @@ __global__ __launch_bounds__(kFinThreads) void counts_finalize(FinalParams p,
 }
 
 size_t jointd_workspace(int32_t d, const int32_t* K, int64_t E);
-size_t jointd_finalize_workspace(int32_t d, const int32_t* K);
+size_t jointd_finalize_workspace(int32_t d, const int32_t* K, int32_t n_sub);
 mp_status jointd_launch(int32_t M, int64_t E, const void* C, const double* n, mp_precision prec,
                         mp_estimator est, int32_t d, const int32_t* bin_of_mode,
                         const int32_t* m_lo, const int32_t* K, int32_t n_sub, int64_t ns,
@@ -736,7 +736,7 @@ mp_status jointd_finalize(int32_t d, const int32_t* K, int32_t n_sub, int64_t ns
                           size_t ws_bytes, hipStream_t stream);
 
 size_t finalize_workspace(int32_t d, mp_bin_mode mode, const int32_t* K, int32_t n_sub) {
-  if (mode == MP_JOINT && d >= 2) return jointd_finalize_workspace(d, K);
+  if (mode == MP_JOINT && d >= 2) return jointd_finalize_workspace(d, K, n_sub);
   return 0;
 }
 

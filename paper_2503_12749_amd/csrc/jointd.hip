@@ -494,101 +494,197 @@ __global__ __launch_bounds__(256) void jointd_sum_f64(JointDParams p, int tau,
 
 // ---------------------------------------------------------------- finalize
 
-// Lines along axis a (all other indices fixed), G per workgroup (G = 4 for
-// K_a <= 64, 2 for K_a <= 128, else 1; each line owns 256 / G threads, whole
-// waves):
-//   out[.., l_a, ..] = sum_{k_a with in != 0} in[.., k_a, ..] e^{-2 pi i k_a l_a / K_a},
-// with a line's nonzero k_a listed in ascending order (ballot prefix sums
-// over its waves) and the twiddles taken from a shared table of
-// e^{-2 pi i q / K_a} by (k_a l_a mod K_a).  On the last axis the value times
-// `scale` is sub-ensemble s's estimate of P, folded into the running mean
-// (P_re, P_im) and sum of squared deviations (m2) with Welford's update.
-__global__ __launch_bounds__(256) void jointd_axis(const double* __restrict__ in,
-                                                   double* __restrict__ out, int Ka, int G,
-                                                   int64_t n_lines, int64_t stride, int last,
-                                                   double scale, int s,
+// DFT along one axis of a grid, out[.., l, ..] = sum_k in[.., k, ..] e^{-2 pi i k l / K},
+// in two short steps per line: with K = A B, k = B a + b and l = l1 + A l2,
+//   Z[l1][b] = e^{-2 pi i b l1 / K} sum_a in[B a + b] e^{-2 pi i a l1 / A},
+//   out[l1 + A l2] = sum_b Z[l1][b] e^{-2 pi i b l2 / B}:
+// A + B products per point instead of K (A: the largest divisor up to 16 and
+// sqrt(K); a K without one takes the sum directly, A = 1, over the k where a
+// line is not zero).  A thread forms several outputs of a sum from one pass
+// over its terms: a term times its step twiddle per output, a chain of at most
+// 16 rotations from an exact twiddle.  A workgroup holds G lines in LDS,
+// neighbours along the contiguous dimension, one padding element per B so that
+// both steps read without bank conflicts; step 1 works in place.  Workgroups
+// whose lines are all zero (outside the boxes) write zeros.  Bound by the FP64
+// operations and the L2 traffic about equally; one line or two per workgroup
+// with K products per point, one sub-ensemble per launch, took 153 us per axis
+// and sub-ensemble for 128^3 points and 111 us for 1024^2 (now 38 to 46 and 37
+// to 54 us).
+//
+// in and out hold `subs` grids: blockIdx.y for the inner axes; on the last
+// axis a workgroup takes its lines of every sub-ensemble in order, and the
+// value times `scale` is folded into the running mean (P_re, P_im) and sum of
+// squared deviations (m2) with Welford's update.
+struct AxisParams {
+  int K, A, B, G, GP;  // GP: lines' LDS stride (odd)
+  int64_t n_lines, stride, cells;
+  double scale;
+  int s0, subs;
+};
+constexpr int kAxisA = 16;    // longest first sum
+constexpr int kAxisOut = 8;   // outputs per thread of the second sum
+constexpr int kAxisPoints = 2048;  // points per workgroup (G lines), where K allows
+constexpr int kAxisMaxSubs = 1024;  // sub-ensembles per launch
+
+// x / d for 0 <= x < 2^22 and 1 <= d: the FP32 estimate is at most one off
+__device__ inline int fast_div(int x, int d, float inv_d) {
+  int q = (int)((float)x * inv_d);
+  const int r = x - q * d;
+  return q + (r >= d ? 1 : 0) - (r < 0 ? 1 : 0);
+}
+
+template <bool LAST>
+__global__ __launch_bounds__(256) void jointd_axis(AxisParams p, const double* __restrict__ in,
+                                                   double* __restrict__ out,
                                                    double* __restrict__ P_re,
                                                    double* __restrict__ P_im,
                                                    double* __restrict__ m2) {
+  typedef __attribute__((ext_vector_type(2), aligned(8))) double d2u;  // in: any FP64 address
+  typedef __attribute__((ext_vector_type(2))) double d2;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  double* tw = (double*)smem;             // 2 Ka, shared
-  double* lines = tw + 2 * Ka;            // G x 2 Ka
-  int* lists = (int*)(lines + 2 * G * Ka);  // G x Ka
-  __shared__ int wcnt[4];
-  __shared__ int total[4];
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int gsz = 256 / G, g = tid / gsz, gt = tid - g * gsz;
-  const int wpg = gsz / 64, wig = gt >> 6;  // waves per line, wave within the line
-  const int64_t L = (int64_t)blockIdx.x * G + g;
-  const bool active = L < n_lines;
-  const int64_t outer = L / stride, inner = L - outer * stride;
-  const int64_t base = outer * (int64_t)Ka * stride + inner;
-  double* line = lines + 2 * g * Ka;
-  int* list = lists + g * Ka;
-  for (int k = tid; k < Ka; k += 256) {
+  const int K = p.K, A = p.A, B = p.B, G = p.G, GP = p.GP;
+  d2* buf = (d2*)smem;                  // (K + A) x GP
+  d2* tw = buf + (int64_t)(K + A) * GP;  // e^{-2 pi i q / B}, q < B
+  d2* twa = tw + B;                      // e^{-2 pi i q / A}, q < A
+  int* nzb = (int*)(twa + A);            // any line nonzero at k = b mod B
+  const int tid = threadIdx.x;
+  const int64_t L0 = (int64_t)blockIdx.x * G;
+  const int nl = p.n_lines - L0 < G ? (int)(p.n_lines - L0) : G;
+  const float inv_k = 1.0f / (float)K, inv_b = 1.0f / (float)B, inv_g = 1.0f / (float)G;
+  for (int i = tid; i < B + A; i += 256) {
     double sw, cw;
-    sincospi(-2.0 * (double)k / (double)Ka, &sw, &cw);
-    tw[2 * k] = cw;
-    tw[2 * k + 1] = sw;
+    sincospi(i < B ? -2.0 * ((double)i / B) : -2.0 * ((double)(i - B) / A), &sw, &cw);
+    tw[i] = d2{cw, sw};
   }
-  for (int k = gt; k < Ka; k += gsz) {
-    line[2 * k] = active ? in[2 * (base + k * stride)] : 0.0;
-    line[2 * k + 1] = active ? in[2 * (base + k * stride) + 1] : 0.0;
-  }
-  if (gt == 0) total[g] = 0;
-  __syncthreads();
-  for (int k0 = 0; k0 < Ka; k0 += gsz) {  // same trip count in every line
-    const int k = k0 + gt;
-    const bool nz = k < Ka && (line[2 * k] != 0.0 || line[2 * k + 1] != 0.0);
-    const unsigned long long mask = __ballot(nz);
-    const int pre = __popcll(mask & ((1ull << lane) - 1ull));
-    if (lane == 0) wcnt[wave] = __popcll(mask);
-    __syncthreads();
-    int off = total[g];
-    for (int q = 0; q < wig; ++q) off += wcnt[g * wpg + q];
-    if (nz) list[off + pre] = k;
-    __syncthreads();
-    if (gt == 0)
-      for (int q = 0; q < wpg; ++q) total[g] += wcnt[g * wpg + q];
-    __syncthreads();
-  }
-  if (!active) return;
-  const int nnz = total[g];
-  // k l < 2^24 (Ka <= 4096) is exact in FP32: the quotient estimate is off by
-  // at most one, which the correction removes
-  const float inv_k = 1.0f / (float)Ka;
-  for (int l = gt; l < Ka; l += gsz) {
-    double sr = 0.0, si = 0.0;
-    for (int q = 0; q < nnz; ++q) {
-      const int k = list[q];
-      const int kl = k * l;
-      int t = kl - (int)((float)kl * inv_k) * Ka;
-      t += t < 0 ? Ka : 0;
-      t -= t >= Ka ? Ka : 0;
-      const double xr = line[2 * k], xi = line[2 * k + 1];
-      const double cr = tw[2 * t], ci = tw[2 * t + 1];
-      sr += xr * cr - xi * ci;
-      si += xr * ci + xi * cr;
-    }
-    const int64_t cell = base + l * stride;
-    if (!last) {
-      out[2 * cell] = sr;
-      out[2 * cell + 1] = si;
-    } else {
-      const double vr = sr * scale, vi = si * scale;
-      if (s == 0) {
-        P_re[cell] = vr;
-        if (P_im) P_im[cell] = vi;
-        m2[cell] = 0.0;
+  // first element of line g (its elements are p.stride apart)
+  auto line_base = [&](int g) {
+    const int64_t L = L0 + g, outer = L / p.stride;
+    return outer * (int64_t)K * p.stride + (L - outer * p.stride);
+  };
+  const int s_lo = LAST ? 0 : (int)blockIdx.y, s_hi = LAST ? p.subs : s_lo + 1;
+  for (int s = s_lo; s < s_hi; ++s) {
+    const d2u* src = (const d2u*)in + (int64_t)s * p.cells;
+    for (int i = tid; i < B; i += 256) nzb[i] = 0;
+    __syncthreads();  // also: the previous sub-ensemble's lines are consumed
+    bool any = false;
+    for (int i = tid; i < K * G; i += 256) {
+      int k, g;
+      if constexpr (LAST) {  // stride 1: lanes along the line
+        g = fast_div(i, K, inv_k);
+        k = i - g * K;
       } else {
-        const double mean = P_re[cell];
-        const double dr = vr - mean;
-        const double nm = mean + dr / (s + 1);
-        P_re[cell] = nm;
-        if (P_im) P_im[cell] += (vi - P_im[cell]) / (s + 1);
-        m2[cell] += dr * (vr - nm);
+        k = fast_div(i, G, inv_g);
+        g = i - k * G;
+      }
+      d2 v = {0.0, 0.0};
+      if (g < nl) v = src[LAST ? (L0 + g) * K + k : line_base(g) + k * p.stride];
+      const int a = fast_div(k, B, inv_b);
+      buf[(k + a) * GP + g] = v;
+      if (v.x != 0.0 || v.y != 0.0) {  // a NaN counts as nonzero
+        any = true;
+        nzb[k - a * B] = 1;
       }
     }
+    any = __syncthreads_or(any);
+    if (any && A > 1) {
+      for (int it = tid; it < B * G; it += 256) {
+        const int b = fast_div(it, G, inv_g), g = it - b * G;
+        d2* x = buf + b * GP + g;
+        const int pitch = (B + 1) * GP;
+        double zr[kAxisA], zi[kAxisA];
+#pragma unroll
+        for (int u = 0; u < kAxisA; ++u) zr[u] = zi[u] = 0.0;
+        for (int a = 0; a < A; ++a) {
+          const d2 v = x[a * pitch], w = twa[a];
+          double vr = v.x, vi = v.y;
+#pragma unroll
+          for (int u = 0; u < kAxisA; ++u) {
+            if (u >= A) break;
+            zr[u] += vr;
+            zi[u] += vi;
+            const double t = fma(vr, w.x, -(vi * w.y));
+            vi = fma(vr, w.y, vi * w.x);
+            vr = t;
+          }
+        }
+        double sb, cb;
+        sincospi(-2.0 * ((double)b / K), &sb, &cb);
+        double wr = 1.0, wi = 0.0;
+#pragma unroll
+        for (int u = 0; u < kAxisA; ++u) {
+          if (u >= A) break;
+          x[u * pitch] = d2{fma(zr[u], wr, -(zi[u] * wi)), fma(zr[u], wi, zi[u] * wr)};
+          const double t = fma(wr, cb, -(wi * sb));
+          wi = fma(wr, sb, wi * cb);
+          wr = t;
+        }
+      }
+      __syncthreads();
+    }
+    const int AG = A * G, nj = (B + kAxisOut - 1) / kAxisOut;
+    const float inv_ag = 1.0f / (float)AG, inv_a = 1.0f / (float)A;
+    for (int it = tid; it < AG * nj; it += 256) {
+      const int j = fast_div(it, AG, inv_ag), r = it - j * AG;
+      int l1, g;
+      if constexpr (LAST) {
+        g = fast_div(r, A, inv_a);
+        l1 = r - g * A;
+      } else {
+        l1 = fast_div(r, G, inv_g);
+        g = r - l1 * G;
+      }
+      double sr[kAxisOut], si[kAxisOut];
+#pragma unroll
+      for (int u = 0; u < kAxisOut; ++u) sr[u] = si[u] = 0.0;
+      if (any) {
+        const d2* z = buf + l1 * (B + 1) * GP + g;
+        const int l0 = j * kAxisOut;  // < B
+        int q = 0;                    // b l0 mod B
+        for (int b = 0; b < B; ++b) {
+          if (nzb[b]) {
+            const d2 v = z[b * GP], w0 = tw[q], w = tw[b];
+            double vr = fma(v.x, w0.x, -(v.y * w0.y)), vi = fma(v.x, w0.y, v.y * w0.x);
+#pragma unroll
+            for (int u = 0; u < kAxisOut; ++u) {
+              sr[u] += vr;
+              si[u] += vi;
+              const double t = fma(vr, w.x, -(vi * w.y));
+              vi = fma(vr, w.y, vi * w.x);
+              vr = t;
+            }
+          }
+          q += l0;
+          q -= q >= B ? B : 0;
+        }
+      }
+      if (g >= nl) continue;
+      const int64_t base = LAST ? (L0 + g) * K : line_base(g);
+#pragma unroll
+      for (int u = 0; u < kAxisOut; ++u) {
+        const int l2 = j * kAxisOut + u;
+        if (l2 >= B) break;
+        const int64_t cell = base + (l1 + A * l2) * p.stride;
+        if constexpr (!LAST) {
+          ((d2*)out)[(int64_t)s * p.cells + cell] = d2{sr[u], si[u]};
+        } else {
+          const double vr = sr[u] * p.scale, vi = si[u] * p.scale;
+          const int n = p.s0 + s;
+          if (n == 0) {
+            P_re[cell] = vr;
+            if (P_im) P_im[cell] = vi;
+            m2[cell] = 0.0;
+          } else {
+            const double mean = P_re[cell];
+            const double dr = vr - mean;
+            const double nm = mean + dr / (n + 1);
+            P_re[cell] = nm;
+            if (P_im) P_im[cell] += (vi - P_im[cell]) / (n + 1);
+            m2[cell] += dr * (vr - nm);
+          }
+        }
+      }
+    }
+    __syncthreads();
   }
 }
 
@@ -599,6 +695,31 @@ __global__ void jointd_sigma(int64_t cells, int n_sub, double* __restrict__ sigm
 }
 
 int64_t round_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
+
+// Shape of the DFT along axis a of a K[0] x .. x K[d - 1] grid.
+AxisParams axis_params(int32_t d, const int32_t* K, int a, int64_t cells) {
+  AxisParams p{};
+  p.K = K[a];
+  p.A = 1;
+  for (int f = 2; f <= kAxisA && f * f <= p.K; ++f)
+    if (p.K % f == 0) p.A = f;
+  p.B = p.K / p.A;
+  p.stride = 1;
+  for (int b = a + 1; b < d; ++b) p.stride *= K[b];
+  p.cells = cells;
+  p.n_lines = cells / p.K;
+  p.G = 1;
+  while (p.G < 64 && 2 * p.G * p.K <= kAxisPoints) p.G *= 2;
+  p.GP = p.G == 1 ? 1 : p.G + 1;
+  return p;
+}
+
+size_t axis_lds(const AxisParams& p) {
+  return (size_t)(p.K + p.A) * p.GP * 16 + (size_t)(p.A + p.B) * 16 + (size_t)p.B * 4;
+}
+// the largest: one line of a prime K below kAxisMaxK
+constexpr int kAxisMaxLds = (kAxisMaxK + 1) * 16 + (kAxisMaxK + 1) * 16 + kAxisMaxK * 4;
+static_assert(kAxisMaxLds <= 160 * 1024, "LDS of a workgroup");
 
 // Workspace layout of a chunk: band ints, per-sample records, factor tables
 // (FP64 elements for the FP64 path, FP32 otherwise).
@@ -663,10 +784,17 @@ size_t jointd_workspace(int32_t d, const int32_t* K, int64_t E) {
   return layout(p, 8);
 }
 
-size_t jointd_finalize_workspace(int32_t d, const int32_t* K) {
+// Two buffers of one grid per sub-ensemble in flight: as many as fit 64 MiB,
+// at least one (grids beyond 2^21 cells run one sub-ensemble per launch and
+// fill the chip with it).
+size_t jointd_finalize_workspace(int32_t d, const int32_t* K, int32_t n_sub) {
   int64_t cells = 1;
   for (int b = 0; b < d; ++b) cells *= K[b];
-  return (size_t)(256 + 2 * round_up(cells * 16, 256));
+  const int64_t one = round_up(cells * 16, 256);
+  int64_t subs = (64ll << 20) / (2 * one);
+  subs = subs < n_sub ? subs : n_sub;
+  subs = subs < kAxisMaxSubs ? subs : kAxisMaxSubs;
+  return (size_t)(256 + 2 * one * (subs > 1 ? subs : 1));
 }
 
 // part != nullptr: the bin sums come from the occupation-fused GEMM's partials
@@ -745,7 +873,9 @@ mp_status jointd_launch(int32_t M, int64_t E, const void* C, const double* n, mp
 mp_status jointd_finalize(int32_t d, const int32_t* K, int32_t n_sub, int64_t ns,
                           const double* acc, double* P_re, double* P_im, double* sigma, void* ws,
                           size_t ws_bytes, hipStream_t stream) {
-  const size_t need = jointd_finalize_workspace(d, K);
+  // one sub-ensemble at a time needs the least; a larger workspace
+  // (jointd_finalize_workspace with the run's n_sub) takes several per launch
+  const size_t need = jointd_finalize_workspace(d, K, 1);
   MP_CHECK_ARG(ws && ws_bytes >= need, MP_ERR_WORKSPACE,
                "mp_counts_finalize: workspace of %zu bytes needed, %zu given", need, ws_bytes);
   const int kmax = d == 2 ? kAxisMaxK : 1024;
@@ -755,33 +885,40 @@ mp_status jointd_finalize(int32_t d, const int32_t* K, int32_t n_sub, int64_t ns
                  kmax, b, K[b]);
   static bool lds_set = false;
   if (!lds_set) {
-    // a line of the largest grid with its twiddles and index list: 36 B per point
-    const hipError_t e = hipFuncSetAttribute((const void*)jointd_axis,
-                                             hipFuncAttributeMaxDynamicSharedMemorySize,
-                                             36 * kAxisMaxK);
-    MP_CHECK_ARG(e == hipSuccess, MP_ERR_HIP, "mp_counts_finalize: %s", hipGetErrorString(e));
+    for (const void* k : {(const void*)jointd_axis<false>, (const void*)jointd_axis<true>}) {
+      const hipError_t e =
+          hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kAxisMaxLds);
+      MP_CHECK_ARG(e == hipSuccess, MP_ERR_HIP, "mp_counts_finalize: %s", hipGetErrorString(e));
+    }
     lds_set = true;
   }
   int64_t cells = 1;
   for (int b = 0; b < d; ++b) cells *= K[b];
   MP_CHECK_ARG(cells < 0x7fffffff, MP_ERR_UNSUPPORTED,
                "mp_counts_finalize: joint grid of %lld cells exceeds 2^31 - 1", (long long)cells);
-  double* buf[2] = {(double*)((char*)ws + 256),
-                    (double*)((char*)ws + 256 + round_up(cells * 16, 256))};
-  const double scale = 1.0 / ((double)cells * (double)ns);
-  for (int s = 0; s < n_sub; ++s) {
+  const int64_t one = round_up(cells * 16, 256);
+  const int64_t fit = ((int64_t)ws_bytes - 256) / (2 * one);
+  int batch = (int)(fit < n_sub ? fit : n_sub);
+  batch = batch < kAxisMaxSubs ? batch : kAxisMaxSubs;
+  double* buf[2] = {(double*)((char*)ws + 256), (double*)((char*)ws + 256 + batch * one)};
+  AxisParams axis[kJD];
+  for (int a = 0; a < d; ++a) axis[a] = axis_params(d, K, a, cells);
+  for (int s = 0; s < n_sub; s += batch) {
     const double* src = acc + 2 * (int64_t)s * cells;
     for (int a = 0; a < d; ++a) {
-      int64_t stride = 1;
-      for (int b = a + 1; b < d; ++b) stride *= K[b];
-      const int last = a == d - 1;
+      AxisParams& p = axis[a];
+      p.s0 = s;
+      p.subs = n_sub - s < batch ? n_sub - s : batch;
+      p.scale = 1.0 / ((double)cells * (double)ns);
       double* dst = buf[a & 1];
-      const int G = K[a] <= 64 ? 4 : (K[a] <= 128 ? 2 : 1);
-      const int64_t n_lines = cells / K[a];
-      const size_t lds = (size_t)K[a] * (16 + 20 * G);
-      hipLaunchKernelGGL(jointd_axis, dim3((unsigned)((n_lines + G - 1) / G)), dim3(256), lds,
-                         stream, src, dst, K[a], G, n_lines, stride, last, scale, s, P_re, P_im,
-                         sigma);
+      const unsigned groups = (unsigned)((p.n_lines + p.G - 1) / p.G);
+      if (a == d - 1)
+        hipLaunchKernelGGL(jointd_axis<true>, dim3(groups), dim3(256), axis_lds(p), stream, p, src,
+                           (double*)nullptr, P_re, P_im, sigma);
+      else
+        hipLaunchKernelGGL(jointd_axis<false>, dim3(groups, (unsigned)p.subs), dim3(256),
+                           axis_lds(p), stream, p, src, dst, (double*)nullptr, (double*)nullptr,
+                           (double*)nullptr);
       src = dst;
     }
   }

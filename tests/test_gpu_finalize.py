@@ -61,3 +61,32 @@ def test_largest_window_and_marginals():
         ref = np.fft.fft(a[:, lo:hi], axis=1) / (k * ns)
         scale = 2.0 ** -53 * (8 + 32 + k / 16) * np.abs(a[:, lo:hi]).sum(1).max() / (k * ns)
         _check(P[lo:hi], Pi[lo:hi], sigma[lo:hi], ref, scale)
+
+
+# lines with and without a factorisation (primes, 2 x prime, 16 x 16 and more), several lines
+# per workgroup with a remainder, the longest line, one point; each with the least workspace
+# (one sub-ensemble per launch) and with the queried one
+@pytest.mark.parametrize("K", [(1, 1), (7, 1), (16, 16), (17, 64), (100, 257), (3, 4093), (4096, 2),
+                               (1024, 48), (128, 96, 5), (33, 16, 130), (1, 1, 9), (12, 10, 8, 6)])
+@pytest.mark.parametrize("n_sub", [1, 5])
+def test_joint_grid(K, n_sub):
+    import paper_2503_12749_amd as mp
+    d, ns = len(K), 11
+    rng = np.random.default_rng(sum(K) * 10 + n_sub)
+    cells = int(np.prod(K))
+    a = rng.standard_normal((n_sub,) + K) + 1j * rng.standard_normal((n_sub,) + K)
+    for b, k in enumerate(K):  # zero outside a box
+        i = np.arange(k)
+        keep = (np.minimum(i, k - i) <= k // 3).reshape([-1 if q == b + 1 else 1 for q in range(d + 1)])
+        a = a * keep
+    ref = (np.fft.fftn(a, axes=tuple(range(1, d + 1))) / (cells * ns)).reshape(n_sub, -1)
+    # per axis: twiddle chains of 16 and 8 rotations (4 roundings each) and two sums of at
+    # most 16 and K terms
+    scale = 2.0 ** -53 * sum(64 + 32 + 16 + k for k in K) * np.abs(a).reshape(n_sub, -1).sum(1).max()
+    scale /= cells * ns
+    out = []
+    for ws in (mp.mp_finalize_workspace(d, "joint", K, 1), None):
+        out.append(_run(d, "joint", K, n_sub, a, ns, ws))
+        _check(*out[-1], ref, scale)
+    for x, y in zip(*out):
+        assert np.array_equal(x, y, equal_nan=True)
