@@ -54,10 +54,14 @@ struct GroupNet {
   const uint16_t* B;  // sampled amplitudes, hi and lo interleaved in 32-blocks
   float* C;
   int64_t ldm, ncols;
+  int kmodes;  // modes multiplied through (k_modes)
   float out_scale;
   int f8_scale_a;  // MP_SPLIT1T_F8: block scale of the FP8 product's A operand
   FusedOut fo;  // the occupation-fused epilogue's output (C unused then)
 };
+
+// Modes that a GEMM multiplies through (propagate.hip).
+int k_modes(int32_t M, int depth = 64);
 
 // Slots of the fused partials for a set of runs; fills slot_off and returns
 // the total.

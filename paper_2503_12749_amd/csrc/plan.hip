@@ -595,7 +595,8 @@ mp_status mp_plan_create(void** plan, int32_t n_net, const mp_net_desc* nets, mp
         const float sc = ldexpf(1.0f, -split_scale_exp(n.d.M, prec));
         // the T-split sample operand's storage columns: beta from E2 on
         const int64_t cols = ab_columns(e, prec);
-        g[i] = GroupNet{(const uint16_t*)n.packed, (const uint16_t*)n.ab, nullptr, n.ldm, cols, sc,
+        g[i] = GroupNet{(const uint16_t*)n.packed, (const uint16_t*)n.ab, nullptr, n.ldm, cols,
+                        k_modes(n.d.M), sc,
                         prec == MP_SPLIT1T_F8 ? f8_scale_a(n.d.M) : 0, FusedOut{}};
         if (e > 0) {
           const mp_status st = fused_out_setup(n.d.M, e, n.nb, n.bins.data(), n.mode,

@@ -245,7 +245,7 @@ typedef __attribute__((ext_vector_type(2))) double f64x2;
 __global__ __launch_bounds__(kThreads, 1) void gemm_f64_pp(const double* __restrict__ A,
                                                            const double* __restrict__ B,
                                                            double* __restrict__ C, int64_t ldm,
-                                                           int64_t ncols) {
+                                                           int64_t ncols, int kmodes) {
   __shared__ __attribute__((aligned(1024))) double lds[D_NST][D_ROWS * D_BK];
   const int tiles_m = (int)(2 * ldm / D_BM), tiles_n = (int)((ncols + D_BN - 1) / D_BN);
   int tm, tn;
@@ -323,10 +323,10 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_f64_pp(const double* __restr
   // sits between the halves: past it every wave has read all of stage
   // kt & 1 (so it may be refilled) and every wave's loads of slab kt + 1 have
   // landed (so it may be read).
-  const int KT = (int)(ldm / D_BK);
+  const int KT = kmodes / D_BK;
   f64x2 a0[4], b0[8], a1[4], b1[8];
-  // prologue: slabs 0 .. D_NST - 1 in flight (KT >= 8 since ldm is a multiple
-  // of 128), then wait for slab 0: loads complete in order, so the 12 loads
+  // prologue: slabs 0 .. D_NST - 1 in flight (within the row, ldm >= 128, also when
+  // KT is 1 and the second is not multiplied), then wait for slab 0: loads complete in order, so the 12 loads
   // of each younger slab may stay outstanding
 #pragma unroll
   for (int st = 0; st < D_NST; ++st) issue(st, (int64_t)st * D_BK);
@@ -505,7 +505,7 @@ __device__ __attribute__((always_inline)) inline void fused_epilogue(
 template <typename H, bool FUSED, bool PF, int NJ = 4>
 __device__ __attribute__((always_inline)) inline void split_pp_tile(uint16_t (*lds)[4][S_PLANE], const uint16_t* __restrict__ A,
                                      const uint16_t* __restrict__ B, float* __restrict__ C,
-                                     int64_t ldm, int64_t ncols, int64_t m0, int64_t n0,
+                                     int64_t ldm, int64_t ncols, int kmodes, int64_t m0, int64_t n0,
                                      float out_scale, const FusedOut* fo, int tid = -1) {
   typedef typename SplitMfma<H>::frag frag;
   // tid < 0: the kernel's own thread index; else an index made opaque by the
@@ -632,7 +632,7 @@ __device__ __attribute__((always_inline)) inline void split_pp_tile(uint16_t (*l
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  const int KT = (int)(ldm / S_BK);  // >= 4
+  const int KT = kmodes / S_BK;  // >= 2
   // Loads return in issue order, so with PF every slab's stage loads are
   // followed by exactly two prefetch loads and the loop waits for all but
   // those two.
@@ -740,14 +740,14 @@ template <typename H, bool PF>
 __global__ __launch_bounds__(kThreads, 1) void gemm_split_256_pp(const uint16_t* __restrict__ A,
                                                                  const uint16_t* __restrict__ B,
                                                                  float* __restrict__ C,
-                                                                 int64_t ldm, int64_t ncols,
+                                                                 int64_t ldm, int64_t ncols, int kmodes,
                                                                  float out_scale) {
   __shared__ __attribute__((aligned(1024))) uint16_t lds_raw[kSplitLdsElems];
   uint16_t (*lds)[4][S_PLANE] = (uint16_t (*)[4][S_PLANE])lds_raw;
   const int tiles_m = (int)(2 * ldm / S_BM), tiles_n = (int)((ncols + S_BN - 1) / S_BN);
   int tm, tn;
   if (!tile_of_block(tiles_m, tiles_n, tm, tn)) return;
-  split_pp_tile<H, false, PF>(lds, A, B, C, ldm, ncols, (int64_t)tm * S_BM, (int64_t)tn * S_BN,
+  split_pp_tile<H, false, PF>(lds, A, B, C, ldm, ncols, kmodes, (int64_t)tm * S_BM, (int64_t)tn * S_BN,
                               out_scale, nullptr);
 }
 
@@ -756,14 +756,14 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_split_256_pp(const uint16_t*
 template <typename H, bool PF>
 __global__ __launch_bounds__(kThreads, 1) void gemm_split_occ(const uint16_t* __restrict__ A,
                                                               const uint16_t* __restrict__ B,
-                                                              int64_t ldm, int64_t ncols,
+                                                              int64_t ldm, int64_t ncols, int kmodes,
                                                               float out_scale, FusedOut fo) {
   __shared__ __attribute__((aligned(1024))) uint16_t lds_raw[kSplitLdsElems];
   uint16_t (*lds)[4][S_PLANE] = (uint16_t (*)[4][S_PLANE])lds_raw;
   const int tiles_m = (int)(2 * ldm / S_BM), tiles_n = (int)((ncols + S_BN - 1) / S_BN);
   int tm, tn;
   if (!tile_of_block(tiles_m, tiles_n, tm, tn)) return;
-  split_pp_tile<H, true, PF>(lds, A, B, nullptr, ldm, ncols, (int64_t)tm * 128, (int64_t)tn * 128,
+  split_pp_tile<H, true, PF>(lds, A, B, nullptr, ldm, ncols, kmodes, (int64_t)tm * 128, (int64_t)tn * 128,
                              out_scale, &fo);
 }
 
@@ -803,7 +803,7 @@ template <bool FUSED, bool PF, int NST = kSplit1Stages, bool BL = kSplit1Lines,
           bool AL = kSplit1ALines>
 __device__ __attribute__((always_inline)) inline void split1_pp_tile(
     uint16_t* __restrict__ lds, const uint16_t* __restrict__ A, const uint16_t* __restrict__ B,
-    float* __restrict__ C, int64_t ldm, int64_t ncols, int64_t m0, int64_t n0, float out_scale,
+    float* __restrict__ C, int64_t ldm, int64_t ncols, int kmodes, int64_t m0, int64_t n0, float out_scale,
     const FusedOut* fo, int tid = -1) {
   typedef f16x8 frag;
   static_assert(NST >= 2 && NST <= kSplit1Stages, "the LDS array holds kSplit1Stages stages");
@@ -945,7 +945,7 @@ __device__ __attribute__((always_inline)) inline void split1_pp_tile(
   constexpr int kGroup = PF ? 12 + NPF : 12;
   constexpr int kWaitN = kGroup * (NST - 2) + (PF ? NPF : 0);
   static_assert(kWaitN < 64, "vmcnt field");
-  const int KT = (int)(ldm / S_BK);  // >= 4
+  const int KT = kmodes / S_BK;  // >= 2
   issue(0, 0);
 #pragma unroll
   for (int s = 1; s + 1 < NST; ++s) {
@@ -1040,25 +1040,25 @@ template <bool PF>
 __global__ __launch_bounds__(kThreads, 1) void gemm_split1_pp(const uint16_t* __restrict__ A,
                                                               const uint16_t* __restrict__ B,
                                                               float* __restrict__ C, int64_t ldm,
-                                                              int64_t ncols, float out_scale) {
+                                                              int64_t ncols, int kmodes, float out_scale) {
   __shared__ __attribute__((aligned(1024))) uint16_t lds[kSplit1LdsElems];
   const int tiles_m = (int)(2 * ldm / S_BM), tiles_n = (int)((ncols + S_BN - 1) / S_BN);
   int tm, tn;
   if (!tile_of_block(tiles_m, tiles_n, tm, tn)) return;
-  split1_pp_tile<false, PF>(lds, A, B, C, ldm, ncols, (int64_t)tm * S_BM, (int64_t)tn * S_BN,
+  split1_pp_tile<false, PF>(lds, A, B, C, ldm, ncols, kmodes, (int64_t)tm * S_BM, (int64_t)tn * S_BN,
                             out_scale, nullptr);
 }
 
 template <bool PF>
 __global__ __launch_bounds__(kThreads, 1) void gemm_split1_occ(const uint16_t* __restrict__ A,
                                                                const uint16_t* __restrict__ B,
-                                                               int64_t ldm, int64_t ncols,
+                                                               int64_t ldm, int64_t ncols, int kmodes,
                                                                float out_scale, FusedOut fo) {
   __shared__ __attribute__((aligned(1024))) uint16_t lds[kSplit1LdsElems];
   const int tiles_m = (int)(2 * ldm / S_BM), tiles_n = (int)((ncols + S_BN - 1) / S_BN);
   int tm, tn;
   if (!tile_of_block(tiles_m, tiles_n, tm, tn)) return;
-  split1_pp_tile<true, PF>(lds, A, B, nullptr, ldm, ncols, (int64_t)tm * 128, (int64_t)tn * 128,
+  split1_pp_tile<true, PF>(lds, A, B, nullptr, ldm, ncols, kmodes, (int64_t)tm * 128, (int64_t)tn * 128,
                            out_scale, &fo);
 }
 
@@ -1088,7 +1088,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_split1_occ(const uint16_t* _
 template <bool FUSED, bool PF, bool PFA>
 __device__ __attribute__((always_inline)) inline void split1t_pp_tile(
     uint16_t* __restrict__ lds, const uint16_t* __restrict__ A, const uint16_t* __restrict__ B,
-    float* __restrict__ C, int64_t ldm, int64_t ncols, int64_t e_real, int64_t m0, int64_t n0,
+    float* __restrict__ C, int64_t ldm, int64_t ncols, int kmodes, int64_t e_real, int64_t m0, int64_t n0,
     float out_scale, const FusedOut* fo, int tid = -1) {
   typedef f16x8 frag;
   constexpr int NST = kSplit1Stages;
@@ -1192,7 +1192,7 @@ __device__ __attribute__((always_inline)) inline void split1t_pp_tile(
   // the schedule and waits of split1_pp_tile (two stages)
   constexpr int kGroup = PF ? 12 + NPF : 12;
   constexpr int kWaitN = PF ? NPF : 0;
-  const int KT = (int)(ldm / S_BK);  // >= 4
+  const int KT = kmodes / S_BK;  // >= 2
   issue(0, 0);
   wait_vm<0>();  // slab 0 landed
   barrier_no_fence();
@@ -1297,26 +1297,26 @@ template <bool PF>
 __global__ __launch_bounds__(kThreads, 1) void gemm_split1t_pp(const uint16_t* __restrict__ A,
                                                                const uint16_t* __restrict__ B,
                                                                float* __restrict__ C, int64_t ldm,
-                                                               int64_t ncols, int64_t e_real,
+                                                               int64_t ncols, int kmodes, int64_t e_real,
                                                                float out_scale) {
   __shared__ __attribute__((aligned(1024))) uint16_t lds[kSplit1LdsElems];
   const int tiles_m = (int)(2 * ldm / S_BM), tiles_n = (int)((ncols + S_BN - 1) / S_BN);
   int tm, tn;
   if (!tile_of_block<kS1tStepRows, kS1tStepCols>(tiles_m, tiles_n, tm, tn)) return;
-  split1t_pp_tile<false, PF, kSplit1tPfA>(lds, A, B, C, ldm, ncols, e_real, (int64_t)tm * S_BM,
+  split1t_pp_tile<false, PF, kSplit1tPfA>(lds, A, B, C, ldm, ncols, kmodes, e_real, (int64_t)tm * S_BM,
                                           (int64_t)tn * S_BN, out_scale, nullptr);
 }
 
 template <bool PF>
 __global__ __launch_bounds__(kThreads, 1) void gemm_split1t_occ(const uint16_t* __restrict__ A,
                                                                 const uint16_t* __restrict__ B,
-                                                                int64_t ldm, int64_t ncols,
+                                                                int64_t ldm, int64_t ncols, int kmodes,
                                                                 float out_scale, FusedOut fo) {
   __shared__ __attribute__((aligned(1024))) uint16_t lds[kSplit1LdsElems];
   const int tiles_m = (int)(2 * ldm / S_BM), tiles_n = (int)((ncols + S_BN - 1) / S_BN);
   int tm, tn;
   if (!tile_of_block<kS1tStepRows, kS1tStepCols>(tiles_m, tiles_n, tm, tn)) return;
-  split1t_pp_tile<true, PF, kSplit1tPfA>(lds, A, B, nullptr, ldm, ncols, 0, (int64_t)tm * 128,
+  split1t_pp_tile<true, PF, kSplit1tPfA>(lds, A, B, nullptr, ldm, ncols, kmodes, 0, (int64_t)tm * 128,
                                          (int64_t)tn * 128, out_scale, &fo);
 }
 
@@ -1428,7 +1428,7 @@ template <int MODE, bool PF>
 __device__ __attribute__((always_inline)) inline void split1t8_pp_tile(
     char* __restrict__ lds, const uint16_t* __restrict__ A, const uint8_t* __restrict__ A8,
     const uint16_t* __restrict__ B, const uint8_t* __restrict__ B8, float* __restrict__ C,
-    int64_t ldm, int64_t ncols, int64_t e_real, int64_t m0, int64_t n0, float out_scale,
+    int64_t ldm, int64_t ncols, int kmodes, int64_t e_real, int64_t m0, int64_t n0, float out_scale,
     int scale_a, const FusedOut* fo, int tid = -1, const uint16_t* __restrict__ alpha = nullptr,
     const float* __restrict__ diag = nullptr) {
   constexpr bool FUSED = MODE == 1, ROWS_RI = MODE != 0;
@@ -1484,7 +1484,7 @@ __device__ __attribute__((always_inline)) inline void split1t8_pp_tile(
       __builtin_amdgcn_global_load_lds((const void*)(src16[q] + (k0 << 2)),
                                        (lds_void*)(base + (8 * wave + q) * 1024), 16, 0, 0);
   };
-  const int KT = (int)(ldm / S_BK);  // even (ldm is a multiple of 128), >= 4
+  const int KT = kmodes / S_BK;  // even, >= 2
   const int NP = KT / 2;
   // half `hf` of FP8 pair `pair` into buffer pair & 1 (data of pair min(pair, NP - 1))
   auto issue8 = [&](int pair, int hf) {
@@ -1669,7 +1669,7 @@ template <bool PF>
 __global__ __launch_bounds__(kThreads, 1) void gemm_split1t8_pp(const uint16_t* __restrict__ A,
                                                                 const uint16_t* __restrict__ B,
                                                                 float* __restrict__ C, int64_t ldm,
-                                                                int64_t ncols, int64_t e_real,
+                                                                int64_t ncols, int kmodes, int64_t e_real,
                                                                 float out_scale, int scale_a) {
   __shared__ __attribute__((aligned(1024))) char lds[F8_LDS];
   const int tiles_m = (int)(2 * ldm / S_BM), tiles_n = (int)((ncols + S_BN - 1) / S_BN);
@@ -1677,14 +1677,14 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_split1t8_pp(const uint16_t* 
   if (!tile_of_block<kS1tStepRows, kS1tStepCols>(tiles_m, tiles_n, tm, tn)) return;
   const uint8_t* A8 = (const uint8_t*)A + 4 * ldm * ldm;
   const uint8_t* B8 = (const uint8_t*)B + 2 * ncols * ldm;
-  split1t8_pp_tile<0, PF>(lds, A, A8, B, B8, C, ldm, ncols, e_real, (int64_t)tm * S_BM,
+  split1t8_pp_tile<0, PF>(lds, A, A8, B, B8, C, ldm, ncols, kmodes, e_real, (int64_t)tm * S_BM,
                               (int64_t)tn * S_BN, out_scale, scale_a, nullptr);
 }
 
 template <bool PF>
 __global__ __launch_bounds__(kThreads, 1) void gemm_split1t8_occ(const uint16_t* __restrict__ A,
                                                                  const uint16_t* __restrict__ B,
-                                                                 int64_t ldm, int64_t ncols,
+                                                                 int64_t ldm, int64_t ncols, int kmodes,
                                                                  float out_scale, int scale_a,
                                                                  FusedOut fo) {
   __shared__ __attribute__((aligned(1024))) char lds[F8_LDS];
@@ -1693,7 +1693,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_split1t8_occ(const uint16_t*
   if (!tile_of_block<kS1tStepRows, kS1tStepCols>(tiles_m, tiles_n, tm, tn)) return;
   const uint8_t* A8 = (const uint8_t*)A + 4 * ldm * ldm;
   const uint8_t* B8 = (const uint8_t*)B + 2 * ncols * ldm;
-  split1t8_pp_tile<1, PF>(lds, A, A8, B, B8, nullptr, ldm, ncols, 0, (int64_t)tm * 128,
+  split1t8_pp_tile<1, PF>(lds, A, A8, B, B8, nullptr, ldm, ncols, kmodes, 0, (int64_t)tm * 128,
                              (int64_t)tn * 128, out_scale, scale_a, &fo);
 }
 
@@ -1704,13 +1704,13 @@ template <bool PF>
 __global__ __launch_bounds__(kThreads, 1) void gemm_split1t8_bilin(
     const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, const uint8_t* __restrict__ B8,
     const uint16_t* __restrict__ alpha, const float* __restrict__ diag, int64_t ldm,
-    int64_t ncols, float out_scale, int scale_a, FusedOut fo) {
+    int64_t ncols, int kmodes, float out_scale, int scale_a, FusedOut fo) {
   __shared__ __attribute__((aligned(1024))) char lds[F8_LDS];
   const int tiles_m = (int)(2 * ldm / S_BM), tiles_n = (int)((ncols + S_BN - 1) / S_BN);
   int tm, tn;
   if (!tile_of_block<kS1tStepRows, kS1tStepCols>(tiles_m, tiles_n, tm, tn)) return;
   const uint8_t* A8 = (const uint8_t*)A + 4 * ldm * ldm;
-  split1t8_pp_tile<2, PF>(lds, A, A8, B, B8, nullptr, ldm, ncols, 0, (int64_t)tm * 128,
+  split1t8_pp_tile<2, PF>(lds, A, A8, B, B8, nullptr, ldm, ncols, kmodes, 0, (int64_t)tm * 128,
                           (int64_t)tn * S_BN, out_scale, scale_a, &fo, -1, alpha, diag);
 }
 
@@ -1786,7 +1786,7 @@ template <bool FUSED>
 __global__ __launch_bounds__(kThreads, 1) void gemm_f32_pp(const float* __restrict__ A,
                                                            const float* __restrict__ B,
                                                            float* __restrict__ C, int64_t ldm,
-                                                           int64_t ncols, FusedOut fo) {
+                                                           int64_t ncols, int kmodes, FusedOut fo) {
   __shared__ __attribute__((aligned(1024))) float lds[2][2][F_PLANE];
   const int tiles_m = (int)(2 * ldm / S_BM), tiles_n = (int)((ncols + S_BN - 1) / S_BN);
   int tm, tn;
@@ -1861,7 +1861,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_f32_pp(const float* __restri
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  const int KT = (int)(ldm / F_BK);  // >= 4
+  const int KT = kmodes / F_BK;  // >= 2
   issue(0, 0);
   wait_vm<0>();
   barrier_no_fence();
@@ -1969,11 +1969,11 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_split_grouped(const GroupNet
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     if (w.w == 2)  // 256 x 128 tile: 128 modes x 64 samples
-      split_pp_tile<H, true, PF, 2>(lds, g->A, g->B, nullptr, g->ldm, g->ncols,
+      split_pp_tile<H, true, PF, 2>(lds, g->A, g->B, nullptr, g->ldm, g->ncols, g->kmodes,
                                     (int64_t)w.y * 128, (int64_t)w.z * 64, g->out_scale, &g->fo,
                                     tid);
     else
-      split_pp_tile<H, true, PF, 4>(lds, g->A, g->B, nullptr, g->ldm, g->ncols,
+      split_pp_tile<H, true, PF, 4>(lds, g->A, g->B, nullptr, g->ldm, g->ncols, g->kmodes,
                                     (int64_t)w.y * 128, (int64_t)w.z * 128, g->out_scale, &g->fo,
                                     tid);
     __syncthreads();  // the next item reuses the LDS stages
@@ -1994,7 +1994,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_split1_grouped(const GroupNe
     const GroupNet* g = nets + w.x;
     int tid = threadIdx.x;  // opaque per item, as in gemm_split_grouped
     asm volatile("" : "+v"(tid));
-    split1_pp_tile<true, PF>(lds, g->A, g->B, nullptr, g->ldm, g->ncols, (int64_t)w.y * 128,
+    split1_pp_tile<true, PF>(lds, g->A, g->B, nullptr, g->ldm, g->ncols, g->kmodes, (int64_t)w.y * 128,
                              (int64_t)w.z * 128, g->out_scale, &g->fo, tid);
     __syncthreads();  // the next item reuses the LDS stages
   }
@@ -2013,7 +2013,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_split1t_grouped(const GroupN
     const GroupNet* g = nets + w.x;
     int tid = threadIdx.x;  // opaque per item, as in gemm_split_grouped
     asm volatile("" : "+v"(tid));
-    split1t_pp_tile<true, PF, kSplit1tPfA>(lds, g->A, g->B, nullptr, g->ldm, g->ncols, 0,
+    split1t_pp_tile<true, PF, kSplit1tPfA>(lds, g->A, g->B, nullptr, g->ldm, g->ncols, g->kmodes, 0,
                                            (int64_t)w.y * 128, (int64_t)w.z * 128, g->out_scale,
                                            &g->fo, tid);
     __syncthreads();  // the next item reuses the LDS stages
@@ -2035,7 +2035,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_split1t8_grouped(const Group
     asm volatile("" : "+v"(tid));
     const uint8_t* A8 = (const uint8_t*)g->A + 4 * g->ldm * g->ldm;
     const uint8_t* B8 = (const uint8_t*)g->B + 2 * g->ncols * g->ldm;
-    split1t8_pp_tile<1, PF>(lds, g->A, A8, g->B, B8, nullptr, g->ldm, g->ncols, 0,
+    split1t8_pp_tile<1, PF>(lds, g->A, A8, g->B, B8, nullptr, g->ldm, g->ncols, g->kmodes, 0,
                                (int64_t)w.y * 128, (int64_t)w.z * 128, g->out_scale,
                                g->f8_scale_a, &g->fo, tid);
     __syncthreads();  // the next item reuses the LDS stages
@@ -2055,6 +2055,13 @@ size_t propagate_workspace(int32_t M, mp_precision prec) {
     default: return elems * 4;  // hi and lo 16-bit values
   }
 }
+
+// Modes that a GEMM multiplies through: M rounded up to a pair of 32-deep slabs (the
+// FP8 product's depth; 16 for the FP64 kernel), not the whole padded row: the rest
+// of it is zeros, whose products leave every accumulator as it is.  Half of the
+// slabs at M = 16 .. 64, 1000 of 1024 modes at most at M = 1000 (none there), 8000
+// of 8064 at M = 8000.
+int k_modes(int32_t M, int depth) { return (M + depth - 1) / depth * depth; }
 
 static int grid_tiles(int64_t ldm, int64_t ncols, int bm, int bn) {
   return mall_grid_blocks((int)(2 * ldm / bm), (int)((ncols + bn - 1) / bn));
@@ -2126,10 +2133,10 @@ mp_status pack_launch(int32_t M, const double* T, mp_precision prec, void* packe
 // GEMM on an already packed operand (one network).
 template <typename H>
 static void split_gemm(int grid, hipStream_t stream, const void* packed, const void* ab, void* C,
-                       int64_t ldm, int64_t ncols, float scale) {
+                       int64_t ldm, int64_t ncols, int kmodes, float scale) {
   auto kernel = split_prefetch_for(ldm) ? gemm_split_256_pp<H, true> : gemm_split_256_pp<H, false>;
   hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), 0, stream, (const uint16_t*)packed,
-                     (const uint16_t*)ab, (float*)C, ldm, ncols, scale);
+                     (const uint16_t*)ab, (float*)C, ldm, ncols, kmodes, scale);
 }
 
 bool split_prefetch(int64_t ldm) { return split_prefetch_for(ldm); }
@@ -2140,26 +2147,26 @@ mp_status gemm_packed_launch(int32_t M, int64_t E, const void* packed, mp_precis
   switch (prec) {
     case MP_FP64:
       hipLaunchKernelGGL(gemm_f64_pp, dim3(grid_tiles(ldm, ncols, D_BM, D_BN)), dim3(kThreads), 0,
-                         stream, (const double*)packed, (const double*)ab, (double*)C, ldm, ncols);
+                         stream, (const double*)packed, (const double*)ab, (double*)C, ldm, ncols, k_modes(M, D_BK));
       break;
     case MP_FP32:
       hipLaunchKernelGGL(gemm_f32_pp<false>, dim3(grid_tiles(ldm, ncols, S_BM, S_BN)),
                          dim3(kThreads), 0, stream, (const float*)packed, (const float*)ab,
-                         (float*)C, ldm, ncols, FusedOut{});
+                         (float*)C, ldm, ncols, k_modes(M), FusedOut{});
       break;
     case MP_SPLIT_BF16:
-      split_gemm<__bf16>(grid_tiles(ldm, ncols, S_BM, S_BN), stream, packed, ab, C, ldm, ncols,
+      split_gemm<__bf16>(grid_tiles(ldm, ncols, S_BM, S_BN), stream, packed, ab, C, ldm, ncols, k_modes(M),
                          1.0f);
       break;
     case MP_SPLIT_FP16:
-      split_gemm<_Float16>(grid_tiles(ldm, ncols, S_BM, S_BN), stream, packed, ab, C, ldm, ncols,
+      split_gemm<_Float16>(grid_tiles(ldm, ncols, S_BM, S_BN), stream, packed, ab, C, ldm, ncols, k_modes(M),
                            ldexpf(1.0f, -fp16_scale_exp(M)));
       break;
     case MP_SPLIT1_FP16: {
       auto kernel = split_prefetch_for(ldm) ? gemm_split1_pp<true> : gemm_split1_pp<false>;
       hipLaunchKernelGGL(kernel, dim3(grid_tiles(ldm, ncols, S_BM, S_BN)), dim3(kThreads), 0,
                          stream, (const uint16_t*)packed, (const uint16_t*)ab, (float*)C, ldm,
-                         ncols, ldexpf(1.0f, -fp16_scale_exp(M)));
+                         ncols, k_modes(M), ldexpf(1.0f, -fp16_scale_exp(M)));
       break;
     }
     case MP_SPLIT1T_FP16: {
@@ -2167,7 +2174,7 @@ mp_status gemm_packed_launch(int32_t M, int64_t E, const void* packed, mp_precis
       const int64_t scols = 2 * split1t_half(E);
       auto kernel = split_prefetch_for(ldm) ? gemm_split1t_pp<true> : gemm_split1t_pp<false>;
       hipLaunchKernelGGL(kernel, dim3(grid_tiles_s1t(ldm, scols)), dim3(kThreads), 0, stream,
-                         (const uint16_t*)packed, (const uint16_t*)ab, (float*)C, ldm, scols, E,
+                         (const uint16_t*)packed, (const uint16_t*)ab, (float*)C, ldm, scols, k_modes(M), E,
                          ldexpf(1.0f, -fp16_scale_exp(M)));
       break;
     }
@@ -2175,7 +2182,7 @@ mp_status gemm_packed_launch(int32_t M, int64_t E, const void* packed, mp_precis
       const int64_t scols = 2 * split1t_half(E);
       auto kernel = split_prefetch_for(ldm) ? gemm_split1t8_pp<true> : gemm_split1t8_pp<false>;
       hipLaunchKernelGGL(kernel, dim3(grid_tiles_s1t(ldm, scols)), dim3(kThreads), 0, stream,
-                         (const uint16_t*)packed, (const uint16_t*)ab, (float*)C, ldm, scols, E,
+                         (const uint16_t*)packed, (const uint16_t*)ab, (float*)C, ldm, scols, k_modes(M), E,
                          ldexpf(1.0f, -fp16_scale_exp(M)), f8_scale_a(M));
       break;
     }
@@ -2225,32 +2232,32 @@ mp_status gemm_fused_launch(int32_t M, int64_t E, const void* packed, mp_precisi
   switch (prec) {
     case MP_FP32:
       hipLaunchKernelGGL(gemm_f32_pp<true>, dim3(grid), dim3(kThreads), 0, stream,
-                         (const float*)packed, (const float*)ab, (float*)nullptr, ldm, ncols, fo);
+                         (const float*)packed, (const float*)ab, (float*)nullptr, ldm, ncols, k_modes(M), fo);
       break;
     case MP_SPLIT_BF16: {
       auto kernel = split_prefetch_for(ldm) ? gemm_split_occ<__bf16, true> : gemm_split_occ<__bf16, false>;
       hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), 0, stream, (const uint16_t*)packed,
-                         (const uint16_t*)ab, ldm, ncols, 1.0f, fo);
+                         (const uint16_t*)ab, ldm, ncols, k_modes(M), 1.0f, fo);
       break;
     }
     case MP_SPLIT_FP16: {
       auto kernel =
           split_prefetch_for(ldm) ? gemm_split_occ<_Float16, true> : gemm_split_occ<_Float16, false>;
       hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), 0, stream, (const uint16_t*)packed,
-                         (const uint16_t*)ab, ldm, ncols, ldexpf(1.0f, -fp16_scale_exp(M)), fo);
+                         (const uint16_t*)ab, ldm, ncols, k_modes(M), ldexpf(1.0f, -fp16_scale_exp(M)), fo);
       break;
     }
     case MP_SPLIT1_FP16: {
       auto kernel = split_prefetch_for(ldm) ? gemm_split1_occ<true> : gemm_split1_occ<false>;
       hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), 0, stream, (const uint16_t*)packed,
-                         (const uint16_t*)ab, ldm, ncols, ldexpf(1.0f, -fp16_scale_exp(M)), fo);
+                         (const uint16_t*)ab, ldm, ncols, k_modes(M), ldexpf(1.0f, -fp16_scale_exp(M)), fo);
       break;
     }
     case MP_SPLIT1T_FP16: {
       const int64_t scols = 2 * split1t_half(E);  // storage columns, beta from E2 on
       auto kernel = split_prefetch_for(ldm) ? gemm_split1t_occ<true> : gemm_split1t_occ<false>;
       hipLaunchKernelGGL(kernel, dim3(grid_tiles_s1t(ldm, scols)), dim3(kThreads), 0, stream,
-                         (const uint16_t*)packed, (const uint16_t*)ab, ldm, scols,
+                         (const uint16_t*)packed, (const uint16_t*)ab, ldm, scols, k_modes(M),
                          ldexpf(1.0f, -fp16_scale_exp(M)), fo);
       break;
     }
@@ -2258,7 +2265,7 @@ mp_status gemm_fused_launch(int32_t M, int64_t E, const void* packed, mp_precisi
       const int64_t scols = 2 * split1t_half(E);
       auto kernel = split_prefetch_for(ldm) ? gemm_split1t8_occ<true> : gemm_split1t8_occ<false>;
       hipLaunchKernelGGL(kernel, dim3(grid_tiles_s1t(ldm, scols)), dim3(kThreads), 0, stream,
-                         (const uint16_t*)packed, (const uint16_t*)ab, ldm, scols,
+                         (const uint16_t*)packed, (const uint16_t*)ab, ldm, scols, k_modes(M),
                          ldexpf(1.0f, -fp16_scale_exp(M)), f8_scale_a(M), fo);
       break;
     }
@@ -2340,7 +2347,7 @@ mp_status gemm_bilinear_launch(int32_t M, int64_t E, const void* packed, mp_prec
   auto kernel = split_prefetch_for(ldm) ? gemm_split1t8_bilin<true> : gemm_split1t8_bilin<false>;
   const float* diag = (const float*)((const char*)packed + propagate_workspace(M, prec));
   hipLaunchKernelGGL(kernel, dim3(grid_tiles_s1t(ldm, e2)), dim3(kThreads), 0, stream,
-                     (const uint16_t*)packed, B, B8, alpha, diag, ldm, e2,
+                     (const uint16_t*)packed, B, B8, alpha, diag, ldm, e2, k_modes(M),
                      ldexpf(1.0f, -fp16_scale_exp(M)), f8_scale_a(M), fo);
   MP_HIP_LAUNCH_CHECK("mp_propagate_counts_bilinear gemm launch");
   return MP_OK;
