@@ -27,9 +27,10 @@
 
 namespace mp {
 
-constexpr int kSBlk = 64;       // samples per workgroup of the fused kernel
-constexpr int kCountThreads = 256;
-constexpr int kEpt = 4;         // accumulator entries per thread per pass
+constexpr int kSBlk = 64;        // least samples per workgroup of the fused kernel
+constexpr int kSBlkMax = 256;
+constexpr int kCountThreads = 512;
+constexpr int kEpt = 4;          // accumulator entries per thread tested at a time
 constexpr int kMaxDist = MP_MAX_BINS + 1;
 struct CountsParams {
   int M;
@@ -50,6 +51,7 @@ struct CountsParams {
   // block -> (sub-ensemble, tile) arithmetic
   int64_t s_first, s_last;
   int t_first, t_mid, t_last, n_mid;
+  int sblk;         // samples per workgroup, kSBlk .. kSBlkMax
 };
 
 __host__ __device__ inline int64_t sub_lo(const CountsParams& p, int64_t s) {
@@ -79,8 +81,8 @@ __device__ inline void block_samples(const CountsParams& p, int b, int64_t& s, i
     }
   }
   const int64_t a = sub_lo(p, s), z = sub_hi(p, s);
-  lo = a + (int64_t)tile * kSBlk;
-  hi = lo + kSBlk < z ? lo + kSBlk : z;
+  lo = a + (int64_t)tile * p.sblk;
+  hi = lo + p.sblk < z ? lo + p.sblk : z;
 }
 
 // Occupations of one sample: nb[b] = sum of n'_j over the modes of bin b
@@ -126,139 +128,245 @@ __device__ inline void dist_occupation(const CountsParams& p, const double (&nb)
     }
 }
 
-// Sources of a sample's bin sums for counts_fused: the propagated amplitudes C
-// (mp_propagate) or the per-block partials of the occupation-fused GEMM.
+// Sources of a workgroup's bin sums for counts_fused: the propagated amplitudes
+// C (mp_propagate) or the per-block partials of the occupation-fused GEMM.
+// bin_sums leaves nb[i][b] of the samples lo + i (chunk-local k0 + i), i < nsmp,
+// in LDS for every bin b < d, behind a barrier; red is LDS scratch.
+typedef __attribute__((ext_vector_type(2))) double d2;
+
 template <typename CT>
 struct FromC {
   const CT* C;
-  __device__ inline void bin_sums(const CountsParams& p, int64_t k, int lane,
-                                  double (&nb)[MP_MAX_BINS][2]) const {
+  // wave per sample, lanes over modes
+  __device__ inline void bin_sums(const CountsParams& p, int64_t k0, int nsmp,
+                                  d2 (*nb)[kMaxDist], d2*) const {
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int64_t ldc = 2 * p.ldm;
-    sample_bin_sums<CT>(p, C + k * ldc, C + (p.E + k) * ldc, lane, nb);
+    for (int i = wave; i < nsmp; i += kCountThreads / 64) {
+      const int64_t k = k0 + i;
+      if (lane == 0)
+        for (int b = 0; b < p.d; ++b) nb[i][b] = d2{0.0, 0.0};
+      for (int q = 0; q < p.n_runs; ++q) {
+        double re, im;
+        run_sum<CT>(C + k * ldc, C + (p.E + k) * ldc, p.ldm, p.run_lo[q], p.run_hi[q], lane, re, im);
+        if (lane == 0) nb[i][p.run_bin[q]] += d2{re, im};
+      }
+    }
+    __syncthreads();
   }
 };
 
 struct FromPartials {
   const float* part;  // FusedOut layout, E = p.E
-  __device__ inline void bin_sums(const CountsParams& p, int64_t k, int lane,
-                                  double (&nb)[MP_MAX_BINS][2]) const {
-#pragma unroll
-    for (int b = 0; b < MP_MAX_BINS; ++b) nb[b][0] = nb[b][1] = 0.0;
+  // lane per sample, so that the 16-byte partials of neighbouring samples share their
+  // lines (a wave per sample with lanes over slots read each line eight times over);
+  // the waves share out a run's slots
+  __device__ inline void bin_sums(const CountsParams& p, int64_t k0, int nsmp,
+                                  d2 (*nb)[kMaxDist], d2* red) const {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int groups = (nsmp + 63) / 64, split = kCountThreads / 64 / ((p.sblk + 63) / 64);
+    const int g = wave / split, w = wave % split;
+    const int i = 64 * g + lane;
+    for (int e = threadIdx.x; e < nsmp * p.d; e += kCountThreads) nb[e / p.d][e % p.d] = d2{0.0, 0.0};
     int slot0 = 0;
     for (int q = 0; q < p.n_runs; ++q) {
       const int nblk = run_blocks(p.run_lo[q], p.run_hi[q]);
-      double sr, si;
-      run_sum_partials(part, p.E, slot0, nblk, k, lane, sr, si);
-      const int bq = p.run_bin[q];
-#pragma unroll
-      for (int b = 0; b < MP_MAX_BINS; ++b)
-        if (b == bq) {
-          nb[b][0] += sr;
-          nb[b][1] += si;
+      d2 s = {0.0, 0.0};
+      if (g < groups && i < nsmp)
+#pragma unroll 4
+        for (int t = w; t < nblk; t += split) {
+          const float4 v = *(const float4*)(part + ((int64_t)(slot0 + t) * p.E + k0 + i) * 4);
+          s += d2{(double)v.x + (double)v.z, (double)v.y + (double)v.w};
         }
+      red[threadIdx.x] = s;
+      __syncthreads();
+      if (threadIdx.x < nsmp) {
+        const int at = (threadIdx.x / 64) * split * 64 + lane;
+        d2 t = red[at];
+        for (int u = 1; u < split; ++u) t += red[at + 64 * u];
+        nb[threadIdx.x][p.run_bin[q]] += t;
+      }
+      __syncthreads();
       slot0 += nblk;
     }
+    if (p.n_runs == 0) __syncthreads();
   }
 };
 
+// Phase 1: the samples' bin occupations (Src), and their two parity weights.
+// Phase 2: the characteristic function on the window grid, summed over the
+// workgroup's samples.  A term is evaluated only where its exact log-magnitude
+// exceeds kLogEps, which for large occupations leaves the grid points near
+// theta = 0 (first term) and pi (second): the grid points where no sample of the
+// workgroup can reach it, by a bound from the samples' least Re n_q and largest
+// |Im n_q|, are dropped up front, the others listed in LDS, and the threads take
+// that list times groups of the samples, so that every lane has work (with a
+// fixed grid point per thread, 256 of 1408 points active at M = 1000 kept one or
+// two of four waves busy).  The groups' sums meet in LDS in order.
+// Bound by phase 1's loads (from C: 16 bytes per mode and sample) and the
+// exponentials of phase 2.  1e5 samples of M = 1000 from FP32 C, 1408 points:
+// 341 us against 569 us with 64 samples per 256 threads and fixed points;
+// 65536 samples of M = 8000 from partials, 4160 points: 60 against 376 us.
 template <typename Src, bool F64>
 __global__ __launch_bounds__(kCountThreads) void counts_fused(CountsParams p, Src src,
                                                               const double* __restrict__ nglob,
                                                               double* __restrict__ partials) {
-  __shared__ double s_nb[kSBlk][kMaxDist][2];
-  __shared__ double s_c1[kSBlk], s_c2[kSBlk];
-  __shared__ int s_skip2[kSBlk];
+  __shared__ d2 s_nb[kSBlkMax][kMaxDist];
+  __shared__ d2 s_c[kSBlkMax];  // log-weights; the second -inf where the partner underflows
+  __shared__ d2 s_red[kCountThreads];
+  __shared__ int s_list[kCountThreads * kEpt];
+  __shared__ int s_wcnt[kCountThreads / 64];
+  __shared__ double s_bound[kMaxDist][4];  // least Re, largest |Im|, largest c1, c2 + 2 Re
+  __shared__ int s_all;
   int64_t sub, lo, hi;
   block_samples(p, blockIdx.x, sub, lo, hi);
   const int nsmp = (int)(hi - lo);
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
 
-  // Phase 1: per-sample bin occupations n_b (wave per sample, lanes over modes
-  // or over the fused GEMM's block partials).
-  for (int i = wave; i < nsmp; i += kCountThreads / 64) {
-    const int64_t k = lo + i - p.e0;  // chunk-local sample index
-    double nb[MP_MAX_BINS][2];
-    src.bin_sums(p, k, lane, nb);
+  if (tid == 0) s_all = 0;
+  src.bin_sums(p, lo - p.e0, nsmp, s_nb, s_red);
+  if (tid < nsmp) {
+    if (p.n_dist > p.d) {  // the total over the bins
+      d2 t = {0.0, 0.0};
+      for (int b = 0; b < p.d; ++b) t += s_nb[tid][b];
+      s_nb[tid][p.d] = t;
+    }
+    const double n = nglob[lo - p.e0 + tid];
+    bool finite = p.est == MP_PLUS_P || isfinite(n);
+    double mx = 0.0;
+    for (int q = 0; q < p.n_dist; ++q) {
+      const d2 v = s_nb[tid][q];
+      finite = finite && isfinite(v.x) && isfinite(v.y);
+      const double a = sqrt(v.x * v.x + v.y * v.y);
+      mx = a > mx ? a : mx;
+    }
+    d2 c;
+    if (p.est == MP_PLUS_P) {
+      c = d2{finite ? 0.0 : __builtin_nan(""), -INFINITY};
+    } else {
+      double c1, c2;
+      parity_log_weights(n, finite, c1, c2);
+      // |e^{-X}| <= e^{2 |n_b|}: skip the parity partner when it underflows
+      c = d2{c1, 2.0 * mx + c2 < -800.0 ? -INFINITY : c2};
+    }
+    s_c[tid] = c;
+    if (!finite) s_all = 1;  // a sample that is not finite reaches every grid point
+  }
+  __syncthreads();
+  for (int q = wave; q < p.n_dist; q += kCountThreads / 64) {
+    double r = INFINITY, i = 0.0, a = -INFINITY, b = -INFINITY;
+    for (int k = lane; k < nsmp; k += 64) {
+      const d2 v = s_nb[k][q], c = s_c[k];
+      r = fmin(r, v.x);
+      i = fmax(i, fabs(v.y));
+      a = fmax(a, c.x);
+      b = fmax(b, c.y + 2.0 * v.x);
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+      r = fmin(r, __shfl_xor(r, off, 64));
+      i = fmax(i, __shfl_xor(i, off, 64));
+      a = fmax(a, __shfl_xor(a, off, 64));
+      b = fmax(b, __shfl_xor(b, off, 64));
+    }
     if (lane == 0) {
-      for (int q = 0; q < p.n_dist; ++q) dist_occupation(p, nb, q, s_nb[i][q][0], s_nb[i][q][1]);
-      const double n = nglob[k];
-      bool finite = p.est == MP_PLUS_P || isfinite(n);
-      for (int q = 0; q < p.n_dist; ++q)
-        finite = finite && isfinite(s_nb[i][q][0]) && isfinite(s_nb[i][q][1]);
-      if (p.est == MP_PLUS_P) {
-        s_c1[i] = finite ? 0.0 : __builtin_nan("");
-        s_c2[i] = 0.0;
-        s_skip2[i] = 1;
-      } else {
-        parity_log_weights(n, finite, s_c1[i], s_c2[i]);
-        // |e^{-X}| <= e^{2 |n_b|}: skip the parity partner when it underflows
-        double mx = 0.0;
-        for (int q = 0; q < p.n_dist; ++q) {
-          const double a = sqrt(s_nb[i][q][0] * s_nb[i][q][0] + s_nb[i][q][1] * s_nb[i][q][1]);
-          mx = a > mx ? a : mx;
-        }
-        s_skip2[i] = (2.0 * mx + s_c2[i] < -800.0) ? 1 : 0;
-      }
+      s_bound[q][0] = r;
+      s_bound[q][1] = i;
+      s_bound[q][2] = a;
+      s_bound[q][3] = b;
     }
   }
   __syncthreads();
 
-  // Phase 2: characteristic function on the window grid, summed over samples.
   constexpr double kTwoPi = 6.283185307179586476925286766559;
+  const bool all = s_all != 0;
+  auto dist_of = [&](int e) {
+    int q = 0;
+    while (q + 1 < p.n_dist && e >= p.off[q + 1]) ++q;
+    return q;
+  };
+  double* out = partials + (int64_t)blockIdx.x * p.entries * 2;
   for (int base = 0; base < p.entries; base += kCountThreads * kEpt) {
-    double ar[kEpt], ai[kEpt], cm1[kEpt], sn[kEpt], thl[kEpt];
-    int dq[kEpt];
+    // the grid points that some sample may reach, in order
+    int count = 0;
 #pragma unroll
     for (int u = 0; u < kEpt; ++u) {
-      ar[u] = ai[u] = 0.0;
-      const int e = base + threadIdx.x + u * kCountThreads;
-      int q = 0;
-      while (q + 1 < p.n_dist && e >= p.off[q + 1]) ++q;
-      dq[u] = (e < p.entries) ? q : -1;
-      const int K = p.K[q];
-      const int kk = (e < p.entries) ? e - p.off[q] : 0;
-      const double th = kTwoPi * (double)kk / (double)K;
-      double s, c;
-      sincos(th, &s, &c);
-      sn[u] = s;
-      cm1[u] = -2.0 * sin(0.5 * th) * sin(0.5 * th);  // cos(th) - 1 without cancellation
-      const int64_t red = ((int64_t)kk * (int64_t)p.m_lo[q]) % K;
-      thl[u] = kTwoPi * (double)red / (double)K;     // th * m_lo reduced mod 2 pi
-    }
-    for (int i = 0; i < nsmp; ++i) {
-      const double c1 = s_c1[i], c2 = s_c2[i];
-      const bool skip2 = s_skip2[i] != 0;
-#pragma unroll
-      for (int u = 0; u < kEpt; ++u) {
-        if (dq[u] < 0) continue;
-        const double nr = s_nb[i][dq[u]][0], ni = s_nb[i][dq[u]][1];
-        // log-magnitudes of the two terms are xr + c1 and c2 - xr; a term
-        // below e^kLogEps is skipped (a NaN one is kept: it must reach the sums)
-        const double xr = cm1[u] * nr - sn[u] * ni;
-        const bool t1 = !(xr + c1 <= kLogEps), t2 = !skip2 && !(c2 - xr <= kLogEps);
-        if (!(t1 || t2)) continue;
-        const double xi = cm1[u] * ni + sn[u] * nr;
-        double tr, ti;
-        if (t1) {
-          cis_exp<F64>(xr + c1, xi - thl[u], tr, ti);
-          ar[u] += tr;
-          ai[u] += ti;
-        }
-        if (t2) {
-          cis_exp<F64>(c2 - xr, -xi - thl[u], tr, ti);
-          ar[u] += tr;
-          ai[u] += ti;
-        }
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < kEpt; ++u) {
-      const int e = base + threadIdx.x + u * kCountThreads;
+      const int e = base + u * kCountThreads + tid;
+      bool in = false;
       if (e < p.entries) {
-        double* dst = partials + ((int64_t)blockIdx.x * p.entries + e) * 2;
-        dst[0] = ar[u];
-        dst[1] = ai[u];
+        const int q = dist_of(e);
+        const double th = kTwoPi * (double)(e - p.off[q]) / (double)p.K[q];
+        // in FP32 with a margin of 1: |log-magnitudes| that matter are below 2^13 times a
+        // few ulps, and the bound only has to include every point that the exact test takes
+        const float sh = sinf((float)(0.5 * th)), ch = cosf((float)(0.5 * th));
+        const double one_minus = 2.0 * (double)sh * sh, one_plus = 2.0 * (double)ch * ch;
+        const double sn = 2.0 * fabs((double)sh * ch);
+        const double* bd = s_bound[q];
+        const double slack = 1.0 + 1e-5 * (fabs(bd[0]) + bd[1]);
+        in = all || bd[2] - one_minus * bd[0] + sn * bd[1] + slack > kLogEps ||
+             bd[3] - one_plus * bd[0] + sn * bd[1] + slack > kLogEps;
+        if (!in) {
+          out[2 * (int64_t)e] = 0.0;
+          out[2 * (int64_t)e + 1] = 0.0;
+        }
       }
+      const unsigned long long mask = __ballot(in);
+      if (lane == 0) s_wcnt[wave] = __popcll(mask);
+      __syncthreads();
+      int at = count;
+#pragma unroll
+      for (int w = 0; w < kCountThreads / 64; ++w) {
+        at += w < wave ? s_wcnt[w] : 0;
+        count += s_wcnt[w];
+      }
+      if (in) s_list[at + __popcll(mask & ((1ull << lane) - 1ull))] = e;
+      __syncthreads();
+    }
+    for (int a0 = 0; a0 < count; a0 += kCountThreads) {
+      // `groups` threads per listed point, each with every groups-th sample
+      const int na = count - a0 < kCountThreads ? count - a0 : kCountThreads;
+      int groups = 1;
+      while (2 * groups * na <= kCountThreads && groups < nsmp) groups *= 2;
+      const int g = tid / na, ai = tid - g * na;
+      d2 sum = {0.0, 0.0};
+      int e = 0;
+      if (g < groups) {
+        e = s_list[a0 + ai];
+        const int q = dist_of(e), K = p.K[q], kk = e - p.off[q];
+        const double th = kTwoPi * (double)kk / (double)K;
+        double sn, cs;
+        sincos(th, &sn, &cs);
+        const double sh = sin(0.5 * th);
+        const double cm1 = -2.0 * sh * sh;  // cos(th) - 1 without cancellation
+        const int64_t red = ((int64_t)kk * (int64_t)p.m_lo[q]) % K;
+        const double thl = kTwoPi * (double)red / (double)K;  // th * m_lo reduced mod 2 pi
+        for (int i = g; i < nsmp; i += groups) {
+          const d2 v = s_nb[i][q], c = s_c[i];
+          // log-magnitudes of the two terms are xr + c1 and c2 - xr; a term
+          // below e^kLogEps is skipped (a NaN one is kept: it must reach the sums)
+          const double xr = cm1 * v.x - sn * v.y;
+          const bool t1 = !(xr + c.x <= kLogEps), t2 = c.y != -INFINITY && !(c.y - xr <= kLogEps);
+          if (!(t1 || t2)) continue;
+          const double xi = cm1 * v.y + sn * v.x;
+          double tr, ti;
+          if (t1) {
+            cis_exp<F64>(xr + c.x, xi - thl, tr, ti);
+            sum += d2{tr, ti};
+          }
+          if (t2) {
+            cis_exp<F64>(c.y - xr, -xi - thl, tr, ti);
+            sum += d2{tr, ti};
+          }
+        }
+      }
+      s_red[tid] = sum;
+      __syncthreads();
+      if (tid < na) {
+        for (int u = 1; u < groups; ++u) sum += s_red[tid + u * na];
+        out[2 * (int64_t)e] = sum.x;
+        out[2 * (int64_t)e + 1] = sum.y;
+      }
+      __syncthreads();
     }
   }
 }
@@ -830,13 +938,15 @@ int64_t acc_entries(int32_t d, mp_bin_mode mode, const int32_t* K) {
   return entries_of(d, mode, K);
 }
 
-// Fills the tiling part of the parameters; returns the number of blocks.
-static int64_t plan_tiles(CountsParams& p) {
+// Fills the tiling part of the parameters for workgroups of `sblk` samples;
+// returns the number of workgroups.  Workspace sizes are those of kSBlk.
+static int64_t plan_tiles(CountsParams& p, int sblk) {
+  p.sblk = sblk;
   p.s_first = p.e0 / p.ns;
   p.s_last = (p.e0 + p.E - 1) / p.ns;
-  auto tiles = [&](int64_t s) { return (int)((sub_hi(p, s) - sub_lo(p, s) + kSBlk - 1) / kSBlk); };
+  auto tiles = [&](int64_t s) { return (int)((sub_hi(p, s) - sub_lo(p, s) + p.sblk - 1) / p.sblk); };
   p.t_first = tiles(p.s_first);
-  p.t_mid = (int)((p.ns + kSBlk - 1) / kSBlk);
+  p.t_mid = (int)((p.ns + p.sblk - 1) / p.sblk);
   p.n_mid = p.s_last > p.s_first + 1 ? (int)(p.s_last - p.s_first - 1) : 0;
   p.t_last = p.s_last != p.s_first ? tiles(p.s_last) : 0;
   return (int64_t)p.t_first + (int64_t)p.n_mid * p.t_mid + p.t_last;
@@ -871,7 +981,7 @@ size_t binned_workspace(int32_t d, mp_bin_mode mode, const int32_t* K, int64_t E
   p.E = E;
   p.e0 = e0;
   p.ns = ns;
-  const int64_t blocks = plan_tiles(p);
+  const int64_t blocks = plan_tiles(p, kSBlk);
   return (size_t)blocks * (size_t)entries_of(d, mode, K) * 16;
 }
 
@@ -901,7 +1011,7 @@ static mp_status setup_counts(CountsParams& p, const char* who, int32_t M, int64
     p.off[q + 1] = p.off[q] + K[q];
   }
   p.entries = p.off[p.n_dist];
-  blocks = plan_tiles(p);
+  blocks = plan_tiles(p, kSBlk);
   if (p.s_last >= n_sub) {
     set_error("%s: samples [%lld, %lld) exceed n_sub * samples_per_sub = %lld", who,
               (long long)e0, (long long)(e0 + E), (long long)n_sub * ns);
@@ -911,6 +1021,38 @@ static mp_status setup_counts(CountsParams& p, const char* who, int32_t M, int64
     set_error("%s: chunk too large", who);
     return MP_ERR_UNSUPPORTED;
   }
+  return MP_OK;
+}
+
+// Samples per workgroup of counts_fused: two workgroups run per CU, so the chunk's
+// sub-ensembles are cut into just under 512 r equal tiles, r the least that keeps
+// them within kSBlkMax samples (more per workgroup share the search for active grid
+// points and write fewer partials, 16 bytes per entry each, read back by
+// counts_reduce); short chunks keep kSBlk.  1e5 samples of M = 1000 in ten
+// sub-ensembles: 341 us with 510 workgroups of 197, 369 us with 790 of 128 (a
+// second turn half empty).
+static int counts_block(const CountsParams& p) {
+  const int64_t subs = p.s_last - p.s_first + 1, len = p.ns < p.E ? p.ns : p.E;
+  for (int64_t r = 1;; ++r) {
+    const int64_t tiles = 512 * r / subs;
+    if (tiles < 1) continue;
+    const int64_t s = (len + tiles - 1) / tiles;
+    if (s <= kSBlkMax) return s < kSBlk ? kSBlk : (int)s;
+  }
+}
+
+// Runs counts_fused and counts_reduce.
+template <typename Src, bool F64>
+static mp_status counts_go(const char* who, CountsParams& p, Src src, const double* n, double* part,
+                           double* acc, hipStream_t stream) {
+  const int64_t blocks = plan_tiles(p, counts_block(p));
+  hipLaunchKernelGGL((counts_fused<Src, F64>), dim3((unsigned)blocks), dim3(kCountThreads), 0, stream,
+                     p, src, n, part);
+  const int ns_touched = (int)(p.s_last - p.s_first + 1);
+  hipLaunchKernelGGL(counts_reduce, dim3((p.entries + 255) / 256, ns_touched), dim3(256), 0, stream,
+                     p, (const double*)part, acc);
+  const hipError_t e = hipGetLastError();
+  MP_CHECK_ARG(e == hipSuccess, MP_ERR_HIP, "%s counts launch: %s", who, hipGetErrorString(e));
   return MP_OK;
 }
 
@@ -935,21 +1077,11 @@ mp_status binned_counts_launch(int32_t M, int64_t E, const void* C, const double
   const size_t need = (size_t)blocks * (size_t)p.entries * 16;
   MP_CHECK_ARG(ws && ws_bytes >= need, MP_ERR_WORKSPACE,
                "mp_binned_counts: workspace of %zu bytes needed, %zu given", need, ws_bytes);
-  if (prec == MP_FP64) {
-    hipLaunchKernelGGL((counts_fused<FromC<double>, true>), dim3((unsigned)blocks),
-                       dim3(kCountThreads), 0, stream, p, FromC<double>{(const double*)C}, n,
-                       (double*)ws);
-  } else {
-    hipLaunchKernelGGL((counts_fused<FromC<float>, false>), dim3((unsigned)blocks),
-                       dim3(kCountThreads), 0, stream, p, FromC<float>{(const float*)C}, n,
-                       (double*)ws);
-  }
-  MP_HIP_LAUNCH_CHECK("mp_binned_counts fused launch");
-  const int ns_touched = (int)(p.s_last - p.s_first + 1);
-  hipLaunchKernelGGL(counts_reduce, dim3((p.entries + 255) / 256, ns_touched), dim3(256), 0, stream,
-                     p, (const double*)ws, acc);
-  MP_HIP_LAUNCH_CHECK("mp_binned_counts reduce launch");
-  return MP_OK;
+  if (prec == MP_FP64)
+    return counts_go<FromC<double>, true>("mp_binned_counts", p, FromC<double>{(const double*)C}, n,
+                                          (double*)ws, acc, stream);
+  return counts_go<FromC<float>, false>("mp_binned_counts", p, FromC<float>{(const float*)C}, n,
+                                        (double*)ws, acc, stream);
 }
 
 mp_status gemm_fused_launch(int32_t M, int64_t E, const void* packed, mp_precision prec,
@@ -1087,15 +1219,8 @@ mp_status counts_from_partials_launch(int32_t M, int64_t E, const double* n, mp_
   propagate_counts_sizes(p, blocks, part_bytes, total);
   MP_CHECK_ARG(ws && ws_bytes >= total, MP_ERR_WORKSPACE,
                "mp_propagate_counts: workspace of %zu bytes needed, %zu given", total, ws_bytes);
-  double* blk = (double*)((char*)ws + part_bytes);
-  hipLaunchKernelGGL((counts_fused<FromPartials, false>), dim3((unsigned)blocks),
-                     dim3(kCountThreads), 0, stream, p, FromPartials{(const float*)ws}, n, blk);
-  MP_HIP_LAUNCH_CHECK("mp_propagate_counts counts launch");
-  const int ns_touched = (int)(p.s_last - p.s_first + 1);
-  hipLaunchKernelGGL(counts_reduce, dim3((p.entries + 255) / 256, ns_touched), dim3(256), 0, stream,
-                     p, (const double*)blk, acc);
-  MP_HIP_LAUNCH_CHECK("mp_propagate_counts reduce launch");
-  return MP_OK;
+  return counts_go<FromPartials, false>("mp_propagate_counts", p, FromPartials{(const float*)ws}, n,
+                                        (double*)((char*)ws + part_bytes), acc, stream);
 }
 
 mp_status propagate_counts_launch(int32_t M, int64_t E, mp_precision prec, mp_estimator est,
