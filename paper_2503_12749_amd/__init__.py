@@ -308,9 +308,9 @@ class CountsPipeline:
                                                     self.K, self.n_sub, self.ns, 0)
         self.ws_counts = torch.empty(wbytes, dtype=torch.uint8, device=dev)
         self.acc = torch.zeros(self.n_sub * self.entries * 2, dtype=torch.float64, device=dev)
-        self.P_re = torch.empty(self.entries, dtype=torch.float64, device=dev)
-        self.P_im = torch.empty(self.entries, dtype=torch.float64, device=dev)
-        self.sigma = torch.empty(self.entries, dtype=torch.float64, device=dev)
+        # side by side: result() checks and copies them together
+        self.P_re, self.P_im, self.sigma = torch.empty(
+            3 * self.entries, dtype=torch.float64, device=dev).split(self.entries)
         fw = mp_finalize_workspace(self.d, self.mode, self.K, self.n_sub)
         self.ws_final = torch.empty(fw, dtype=torch.uint8, device=dev) if fw else None
 
@@ -382,9 +382,22 @@ class CountsPipeline:
         """(P_re, P_im, sigma) as numpy arrays (synchronises); raises MPError
         (MP_ERR_NONFINITE) if the estimate holds NaN or infinite values."""
         scratch = self.torch.empty(1, dtype=self.torch.int64, device=self.P_re.device)
-        mp_check_finite(self.P_re, scratch)
-        mp_check_finite(self.P_im, scratch)
-        return (self.P_re.cpu().numpy(), self.P_im.cpu().numpy(), self.sigma.cpu().numpy())
+        e, arrays = self.entries, (self.P_re, self.P_im, self.sigma)
+        at = [a.data_ptr() - arrays[0].data_ptr() for a in arrays]
+        same = len({a.untyped_storage().data_ptr() for a in arrays}) == 1
+        if same and at == [0, 8 * e, 16 * e]:  # as __init__ lays them out: one check, one copy
+            both = arrays[0].as_strided((3 * e,), (1,))
+            try:
+                mp_check_finite(both[: 2 * e], scratch)
+            except MPError:
+                for a in arrays[:2]:  # the error of the array that holds them
+                    mp_check_finite(a, scratch)
+                raise
+            host = both.cpu().numpy()
+            return tuple(host[q * e: (q + 1) * e].copy() for q in range(3))
+        for a in arrays[:2]:
+            mp_check_finite(a, scratch)
+        return tuple(a.cpu().numpy() for a in arrays)
 
     def alpha_beta(self, E: int):
         """Views of the last chunk's stored amplitudes as numpy (E, M) arrays
@@ -577,17 +590,23 @@ class Plan:
         t.cuda.synchronize()
         K = self.K[i]
         scratch = t.empty(1, dtype=t.int64, device=self.device)
-        for ptr in (pr, pi):
-            _lib.check(_lib.load().mp_check_finite(ctypes.c_void_p(ptr.value), K, _ptr(scratch),
-                                                   None, None))
-        out = []
+        lib = _lib.load()
+
+        def check(ptr, n):
+            return lib.mp_check_finite(ctypes.c_void_p(ptr.value), n, _ptr(scratch), None, None)
+        # the plan keeps the three arrays side by side: one check and one copy
+        together = pi.value == pr.value + 8 * K and sg.value == pr.value + 16 * K
+        if not together or check(pr, 2 * K) != _lib.MP_OK:
+            for ptr in (pr, pi):
+                _lib.check(check(ptr, K))
+        out = np.empty((3, K), dtype=np.float64)
         hip = _hip_runtime()
-        for ptr in (pr, pi, sg):
-            buf = (ctypes.c_double * K)()
-            if hip.hipMemcpy(buf, ctypes.c_void_p(ptr.value), ctypes.c_size_t(8 * K), 2) != 0:
+        parts = [(pr, out)] if together else list(zip((pr, pi, sg), out))
+        for ptr, dst in parts:
+            if hip.hipMemcpy(ctypes.c_void_p(dst.ctypes.data), ctypes.c_void_p(ptr.value),
+                             ctypes.c_size_t(dst.nbytes), 2) != 0:
                 raise MPError(-3, "hipMemcpy of plan results failed")
-            out.append(np.frombuffer(buf, dtype=np.float64).copy())
-        return tuple(out)
+        return tuple(row.copy() for row in out)
 
     def info(self):
         o, f, ms, b = ctypes.c_int32(), ctypes.c_int32(), ctypes.c_double(), ctypes.c_size_t()

@@ -7,6 +7,8 @@ from __future__ import annotations
 import ctypes
 import os
 
+import numpy as np
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libmpgbs.so")
 
@@ -154,5 +156,7 @@ def check(status: int) -> None:
 
 
 def i32_array(values) -> ctypes.Array:
+    if isinstance(values, np.ndarray) and values.dtype == np.int32 and values.ndim == 1 and values.size:
+        return (ctypes.c_int32 * values.size).from_buffer_copy(np.ascontiguousarray(values))
     vals = [int(v) for v in values]
     return (ctypes.c_int32 * max(1, len(vals)))(*vals)

@@ -1366,22 +1366,43 @@ __global__ void zero_i64(int64_t* p) {
   if (threadIdx.x == 0) *p = 0;
 }
 
-// Grid-stride count of non-finite entries, one atomic add per wave.
-__global__ __launch_bounds__(256) void count_nonfinite(const double* __restrict__ x, int64_t n,
-                                                       int64_t* __restrict__ count) {
+// Grid-stride count of non-finite entries: one atomic add per wave into the cleared
+// counter, or, as one workgroup (`alone`, up to kFiniteAlone values: a launch less),
+// their sum through LDS.
+constexpr int64_t kFiniteAlone = 32768;
+
+__global__ __launch_bounds__(1024) void count_nonfinite(const double* __restrict__ x, int64_t n,
+                                                        bool alone, int64_t* __restrict__ count) {
+  __shared__ int64_t part[16];
   int64_t c = 0;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * blockDim.x)
     c += isfinite(x[i]) ? 0 : 1;
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off, 64);
-  if ((threadIdx.x & 63) == 0 && c != 0) atomicAdd((unsigned long long*)count, (unsigned long long)c);
+  if (!alone) {
+    if ((threadIdx.x & 63) == 0 && c != 0)
+      atomicAdd((unsigned long long*)count, (unsigned long long)c);
+    return;
+  }
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = c;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < (int)blockDim.x / 64; ++w) c += part[w];
+    *count = c;
+  }
 }
 
 mp_status check_finite_launch(const double* x, int64_t n, int64_t* scratch, int64_t* n_bad,
                               hipStream_t stream) {
-  hipLaunchKernelGGL(zero_i64, dim3(1), dim3(64), 0, stream, scratch);
-  const int64_t blocks = (n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096;
-  hipLaunchKernelGGL(count_nonfinite, dim3((unsigned)blocks), dim3(256), 0, stream, x, n, scratch);
+  if (n <= kFiniteAlone) {
+    hipLaunchKernelGGL(count_nonfinite, dim3(1), dim3(1024), 0, stream, x, n, true, scratch);
+  } else {
+    hipLaunchKernelGGL(zero_i64, dim3(1), dim3(64), 0, stream, scratch);
+    const int64_t blocks = (n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096;
+    hipLaunchKernelGGL(count_nonfinite, dim3((unsigned)blocks), dim3(256), 0, stream, x, n, false,
+                       scratch);
+  }
   MP_HIP_LAUNCH_CHECK("mp_check_finite launch");
   int64_t c = 0;
   hipError_t e = hipMemcpyAsync(&c, scratch, sizeof(c), hipMemcpyDeviceToHost, stream);

@@ -545,9 +545,10 @@ mp_status mp_plan_create(void** plan, int32_t n_net, const mp_net_desc* nets, mp
     n.r = (double*)plan_alloc(p, (size_t)n.d.M * 8);
     n.n = (double*)plan_alloc(p, (size_t)n.chunk * 8);
     n.acc = (double*)plan_alloc(p, (size_t)n.d.n_sub * n.entries * 16);
-    n.P_re = (double*)plan_alloc(p, (size_t)n.entries * 8);
-    n.P_im = (double*)plan_alloc(p, (size_t)n.entries * 8);
-    n.sigma = (double*)plan_alloc(p, (size_t)n.entries * 8);
+    // side by side, so that a caller can check and copy them together
+    n.P_re = (double*)plan_alloc(p, (size_t)n.entries * 24);
+    n.P_im = n.P_re ? n.P_re + n.entries : nullptr;
+    n.sigma = n.P_re ? n.P_im + n.entries : nullptr;
     n.ws_fin_bytes = finalize_workspace(n.nb, n.mode, n.K.data(), n.d.n_sub);
     if (n.ws_fin_bytes) n.ws_fin = plan_alloc(p, n.ws_fin_bytes);
     n.ab = plan_alloc(p, (size_t)n.ldm * ab_columns(n.chunk, prec) * elem_bytes_ab(prec));
