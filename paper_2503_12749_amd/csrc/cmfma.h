@@ -69,35 +69,45 @@ __device__ __attribute__((always_inline)) inline void slab(const float* are, con
 }
 
 // Three-product form of one slab: P1 += Ar Br^T, P2 += Ai Bi^T,
-// P3 += (Ar + Ai)(Br + Bi)^T, so that Re = P1 - P2 and Im = P3 - P1 - P2.
+// P3 += (Ar + Ai)(Br + Bi)^T, so that Re = P1 - P2 and Im = P3 - P1 - P2.  The
+// next samples' fragments are read ahead of the products.
 __device__ __attribute__((always_inline)) inline void slab3(const float* are, const float* aim,
                                                              const float* bre, const float* bim,
                                                              int wi, int wj, int lane,
                                                              f32x16 (&p1)[2][2], f32x16 (&p2)[2][2],
                                                              f32x16 (&p3)[2][2]) {
   const int lr = lane & 31, lh = lane >> 5;
-#pragma unroll 4
+  const float* pa[2] = {are + lh * kTile + 64 * wi + lr, aim + lh * kTile + 64 * wi + lr};
+  const float* pb[2] = {bre + lh * kTile + 64 * wj + lr, bim + lh * kTile + 64 * wj + lr};
+  float x[2][2], y[2][2], nx[2][2], ny[2][2];  // [re, im][block]
+  auto read = [&](int t, float(&u)[2][2], float(&v)[2][2]) {
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int a = 0; a < 2; ++a) {
+        u[c][a] = pa[c][2 * t * kTile + 32 * a];
+        v[c][a] = pb[c][2 * t * kTile + 32 * a];
+      }
+  };
+  read(0, x, y);
+#pragma unroll
   for (int t = 0; t < kSlab / 2; ++t) {
-    const int kk = 2 * t + lh;
-    float ar[2], ai[2], br[2], bi[2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a) {
-      ar[a] = are[kk * kTile + 64 * wi + 32 * a + lr];
-      ai[a] = aim[kk * kTile + 64 * wi + 32 * a + lr];
-    }
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      br[b] = bre[kk * kTile + 64 * wj + 32 * b + lr];
-      bi[b] = bim[kk * kTile + 64 * wj + 32 * b + lr];
-    }
+    if (t + 1 < kSlab / 2) read(t + 1, nx, ny);
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
       for (int b = 0; b < 2; ++b) {
-        p1[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(ar[a], br[b], p1[a][b], 0, 0, 0);
-        p2[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(ai[a], bi[b], p2[a][b], 0, 0, 0);
-        p3[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(ar[a] + ai[a], br[b] + bi[b], p3[a][b], 0,
-                                                        0, 0);
+        p1[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[0][a], y[0][b], p1[a][b], 0, 0, 0);
+        p2[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[1][a], y[1][b], p2[a][b], 0, 0, 0);
+        p3[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[0][a] + x[1][a], y[0][b] + y[1][b],
+                                                        p3[a][b], 0, 0, 0);
+      }
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int a = 0; a < 2; ++a) {
+        x[c][a] = nx[c][a];
+        y[c][a] = ny[c][a];
       }
   }
 }

@@ -30,6 +30,7 @@ namespace mp {
 
 namespace {
 
+typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 using cmfma::f32x16;
 typedef __attribute__((ext_vector_type(4))) double f64x4;
@@ -131,59 +132,62 @@ static_assert(PT == cmfma::kTile && PK == cmfma::kSlab, "tile shape of the share
 // with three real products per fragment pair instead of four:
 //   P1 = Xr_I Xr_J^T,  P2 = Xi_I Xi_J^T,  P3 = (Xr + Xi)_I (Xr + Xi)_J^T,
 //   Re = P1 - P2,      Im = P3 - P1 - P2.
-// 25 % fewer MFMAs; the third accumulator set leaves one workgroup per CU
-// (measured at M = 1000: 3.53 ms per chunk against 3.88 ms for the four-
-// product form at two workgroups per CU).  The FP32 sums then carry rounding
-// of up to 4 K u sum |n'_i||n'_j| in Im (P3 sums (|Re| + |Im|) products)
-// instead of 2 K u.  The next slab is loaded into registers while the
-// current one is multiplied; samples past the sub-ensemble's range are
-// loaded as zeros.
+// 25 % fewer MFMAs; the third accumulator set leaves one workgroup per CU.  The FP32
+// sums carry rounding of up to 4 K u sum |n'_i||n'_j| in Im (P3 sums (|Re| +
+// |Im|) products) instead of 2 K u.  Slabs go from memory straight to LDS
+// (global_load_lds, whole 512-byte sample rows) into two stages, with one barrier
+// per slab: past it slab s has landed and every wave has read slab s - 1, whose
+// stage the loads of slab s + 1 refill.  Samples past the range repeat the last one
+// and are cleared in LDS in the last slab.  Bound by the FP32 matrix cores.  1e5
+// samples of M = 1000: 3.25 ms (MFMA time alone 2.25 ms) against 3.49 ms with slabs
+// staged through registers and two barriers around the LDS writes.
 __global__ __launch_bounds__(256, 1) void pair_corr_f32(PairParams p, const float* __restrict__ X,
                                                        double* __restrict__ acc) {
-  __shared__ __attribute__((aligned(16))) float lds[4][PK][PT];  // Re I, Im I, Re J, Im J
+  __shared__ __attribute__((aligned(1024))) float lds[2][4][PK][PT];  // Re I, Im I, Re J, Im J
   int I, J, pc;
   int64_t s, k0, k1;
   pair_item(p, I, J, s, pc, k0, k1);
   const bool diag = I == J;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int wi = wave >> 1, wj = wave & 1;
 
-  // loader: four consecutive modes of rows lrow + 8 u (u < 4) of each plane
-  const int lc = (tid & 31) * 4, lrow = tid >> 5;
-  const int64_t im_off = p.E * p.ldm;
-  const float* src[4] = {X + I * PT + lc, X + im_off + I * PT + lc, X + J * PT + lc,
-                         X + im_off + J * PT + lc};
-  const int nplanes = diag ? 2 : 4;
-  f32x4 st[4][4];
-  auto load = [&](int64_t kb) {
+  // loader: wave w fills plane w, two sample rows (1 KB) per load; a diagonal tile
+  // multiplies planes 0 and 1 with themselves
+  const float* src = X + (wave & 1 ? p.E * p.ldm : 0) + (wave < 2 ? I : J) * PT + 4 * (lane & 31);
+  auto load = [&](int st, int64_t kb) {
+    if (diag && wave >= 2) return;
 #pragma unroll
-    for (int pl = 0; pl < 4; ++pl)
-      if (pl < nplanes)
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int64_t k = kb + lrow + 8 * u;
-          st[pl][u] = k < k1 ? *(const f32x4*)(src[pl] + k * p.ldm) : f32x4{0.f, 0.f, 0.f, 0.f};
-        }
+    for (int q = 0; q < PK / 2; ++q) {
+      const int64_t k = kb + 2 * q + (lane >> 5);
+      __builtin_amdgcn_global_load_lds((const void*)(src + (k < k1 ? k : k1 - 1) * p.ldm),
+                                       (lds_void*)&lds[st][wave][2 * q][0], 16, 0, 0);
+    }
   };
-  const float* bre = diag ? &lds[0][0][0] : &lds[2][0][0];
-  const float* bim = diag ? &lds[1][0][0] : &lds[3][0][0];
+  const int pj = diag ? 0 : 2;
 
   // P1 = Xr Xr^T, P2 = Xi Xi^T, P3 = (Xr + Xi)(Xr + Xi)^T (in accR, accI, acc3)
   f32x16 accR[2][2], accI[2][2], acc3[2][2];
   cmfma::zero(accR, accI);
   cmfma::zero(acc3, acc3);
 
-  load(k0);
-  for (int64_t kb = k0; kb < k1; kb += PK) {
-    __syncthreads();  // every wave is done with the previous slab
-#pragma unroll
-    for (int pl = 0; pl < 4; ++pl)
-      if (pl < nplanes)
-#pragma unroll
-        for (int u = 0; u < 4; ++u) *(f32x4*)&lds[pl][lrow + 8 * u][lc] = st[pl][u];
-    __syncthreads();
-    if (kb + PK < k1) load(kb + PK);
-    cmfma::slab3(&lds[0][0][0], &lds[1][0][0], bre, bim, wi, wj, lane, accR, accI, acc3);
+  if (k0 < k1) load(0, k0);
+  for (int64_t kb = k0, st = 0; kb < k1; kb += PK, st ^= 1) {
+    // own loads of this slab landed and own reads of the other stage done (the products
+    // of the previous slab consumed them), then everyone's
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    if (kb + PK < k1) load((int)st ^ 1, kb + PK);
+    if (kb + PK > k1) {
+      for (int e = tid; e < (int)(kb + PK - k1) * PT; e += 256) {
+        const int r = (int)(k1 - kb) + e / PT;
+        lds[st][0][r][e % PT] = 0.f;
+        lds[st][1][r][e % PT] = 0.f;
+      }
+      __syncthreads();
+    }
+    cmfma::slab3(&lds[st][0][0][0], &lds[st][1][0][0], &lds[st][pj][0][0], &lds[st][pj + 1][0][0],
+                 wi, wj, lane, accR, accI, acc3);
   }
   // Re = P1 - P2, Im = P3 - P1 - P2
 #pragma unroll
