@@ -136,11 +136,39 @@ __host__ __device__ inline int64_t pair8_offset(int64_t r, int64_t j, int64_t ld
   return (r >> 1) * 2 * ldm + 128 * (j >> 6) + 64 * (r & 1) + (j & 63);
 }
 
-// Wave-wide sums (64 lanes) via cross-lane shuffles.
-__device__ inline double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+// v of the lane that the DPP control names, for both halves of a double.
+template <int CTRL>
+__device__ inline double dpp_f64(double v) {
+  const int2 w = __builtin_bit_cast(int2, v);
+  return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_mov_dpp(w.x, CTRL, 0xF, 0xF, true),
+                                              __builtin_amdgcn_mov_dpp(w.y, CTRL, 0xF, 0xF, true)));
+}
+
+// Sums over the G = 16 or 64 neighbouring lanes of a lane's group, in every lane, on
+// the cross-lane paths of the vector unit (an LDS shuffle per step waits some 100
+// cycles, in a chain of six).
+template <int G>
+__device__ inline double group_sum(double v) {
+  static_assert(G == 16 || G == 64, "a row of 16 lanes or the wave");
+  v += dpp_f64<0xB1>(v);   // lane ^ 1
+  v += dpp_f64<0x4E>(v);   // lane ^ 2
+  v += dpp_f64<0x141>(v);  // 7 - lane of 8: the other four
+  v += dpp_f64<0x140>(v);  // 15 - lane of 16: the other eight
+  if constexpr (G == 64) {
+    // rows (0, 1) and (2, 3) exchanged, then the wave's halves
+    const int2 w = __builtin_bit_cast(int2, v);
+    const auto x = __builtin_amdgcn_permlane16_swap(w.x, w.x, false, false);
+    const auto y = __builtin_amdgcn_permlane16_swap(w.y, w.y, false, false);
+    v = __builtin_bit_cast(double, make_int2(x[0], y[0])) +
+        __builtin_bit_cast(double, make_int2(x[1], y[1]));
+    const int2 u = __builtin_bit_cast(int2, v);
+    const auto c = __builtin_amdgcn_permlane32_swap(u.x, u.x, false, false);
+    const auto d = __builtin_amdgcn_permlane32_swap(u.y, u.y, false, false);
+    v = __builtin_bit_cast(double, make_int2(c[0], d[0])) +
+        __builtin_bit_cast(double, make_int2(c[1], d[1]));
+  }
   return v;
 }
+__device__ inline double wave_sum(double v) { return group_sum<64>(v); }
 
 }  // namespace mp

@@ -85,49 +85,6 @@ __device__ inline void block_samples(const CountsParams& p, int b, int64_t& s, i
   hi = lo + p.sblk < z ? lo + p.sblk : z;
 }
 
-// Occupations of one sample: nb[b] = sum of n'_j over the modes of bin b
-// (every lane holds the wave-reduced sums).
-template <typename CT>
-__device__ inline void sample_bin_sums(const CountsParams& p, const CT* __restrict__ ca,
-                                       const CT* __restrict__ cb, int lane,
-                                       double (&nb)[MP_MAX_BINS][2]) {
-#pragma unroll
-  for (int b = 0; b < MP_MAX_BINS; ++b) nb[b][0] = nb[b][1] = 0.0;
-  for (int q = 0; q < p.n_runs; ++q) {
-    double re, im;
-    run_sum<CT>(ca, cb, p.ldm, p.run_lo[q], p.run_hi[q], lane, re, im);
-    const int bq = p.run_bin[q];
-#pragma unroll
-    for (int b = 0; b < MP_MAX_BINS; ++b)
-      if (b == bq) {
-        nb[b][0] += re;
-        nb[b][1] += im;
-      }
-  }
-}
-
-// Occupation feeding distribution q: bin dist_src[q], or the total over the
-// d bins when dist_src[q] = -1.
-__device__ inline void dist_occupation(const CountsParams& p, const double (&nb)[MP_MAX_BINS][2],
-                                       int q, double& vr, double& vi) {
-  double tr = 0.0, ti = 0.0;
-#pragma unroll
-  for (int b = 0; b < MP_MAX_BINS; ++b)
-    if (b < p.d) {
-      tr += nb[b][0];
-      ti += nb[b][1];
-    }
-  vr = tr;
-  vi = ti;
-  const int src = p.dist_src[q];
-#pragma unroll
-  for (int b = 0; b < MP_MAX_BINS; ++b)
-    if (b == src) {
-      vr = nb[b][0];
-      vi = nb[b][1];
-    }
-}
-
 // Sources of a workgroup's bin sums for counts_fused: the propagated amplitudes
 // C (mp_propagate) or the per-block partials of the occupation-fused GEMM.
 // bin_sums leaves nb[i][b] of the samples lo + i (chunk-local k0 + i), i < nsmp,
@@ -1422,33 +1379,44 @@ mp_status check_finite_launch(const double* x, int64_t n, int64_t* scratch, int6
 
 // ---------------------------------------------------------------- per-sample observables
 
-// Occupation of every distribution for every sample of the chunk (wave per
-// sample): nq[(k n_dist + q) 2 + {0, 1}] = (Re, Im) n_q of chunk sample k.
-template <typename CT>
-__device__ inline void occupation_sample(const CountsParams& p, const CT* __restrict__ C,
-                                         double* __restrict__ nq, int64_t k, int lane) {
-  const int64_t ldc = 2 * p.ldm;
-  double nb[MP_MAX_BINS][2];
-  sample_bin_sums<CT>(p, C + k * ldc, C + (p.E + k) * ldc, lane, nb);
-  if (lane == 0)
-    for (int q = 0; q < p.n_dist; ++q) {
-      double vr, vi;
-      dist_occupation(p, nb, q, vr, vi);
-      nq[(k * p.n_dist + q) * 2] = vr;
-      nq[(k * p.n_dist + q) * 2 + 1] = vi;
-    }
-
-}
-
-template <typename CT>
+// Occupation of every distribution for every sample of the chunk:
+// nq[(k n_dist + q) 2 + {0, 1}] = (Re, Im) n_q of chunk sample k, by G lanes per
+// sample (64: one sample per wave at a time; 16: four).  Lane gl < n_dist of the group
+// adds up distribution gl over the bin runs and writes it.  Bound by memory from
+// some 50 modes on, below that by the chain of loads and reductions over a sample's
+// runs.  FP32, one run of 14 modes, 1.2e5 samples: 13 us (56 us by waves with LDS
+// shuffles); six of 14: 39 us (234); one of 1000, 4e4 samples: 110 us, 5.8 TB/s (123).
+template <typename CT, int G>
 __global__ __launch_bounds__(256) void occupations_kernel(CountsParams p, const CT* __restrict__ C,
                                                           double* __restrict__ nq) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int64_t base = (int64_t)blockIdx.x * (4 * kOccPerWave) + wave;
+  constexpr int S = 64 / G;  // samples per wave at a time
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int gl = lane % G;
+  const int64_t ldc = 2 * p.ldm;
+  int src = -2;  // bin of this lane's distribution, -1 = all
+#pragma unroll
+  for (int q = 0; q < kMaxDist; ++q)
+    if (q == gl && q < p.n_dist) src = p.dist_src[q];
   for (int j = 0; j < kOccPerWave; ++j) {
-    const int64_t k = base + 4 * j;
-    if (k >= p.E) return;
-    occupation_sample<CT>(p, C, nq, k, lane);
+    const int64_t k0 = ((int64_t)blockIdx.x * (4 * kOccPerWave) + 4 * j + wave) * S;
+    if (k0 >= p.E) return;
+    int64_t k = k0 + lane / G;
+    const bool valid = k < p.E;
+    if (!valid) k = k0;
+    double vr = 0.0, vi = 0.0;
+    for (int q = 0; q < p.n_runs; ++q) {
+      double re, im;
+      run_sum<CT, G>(C + k * ldc, C + (p.E + k) * ldc, p.ldm, p.run_lo[q], p.run_hi[q], gl, re, im);
+      if (src == -1 || src == p.run_bin[q]) {
+        vr += re;
+        vi += im;
+      }
+    }
+    if (valid && src != -2) {
+      double* o = nq + (k * p.n_dist + gl) * 2;
+      o[0] = vr;
+      o[1] = vi;
+    }
   }
 }
 
@@ -1608,13 +1576,16 @@ mp_status occupations_launch(int32_t M, int64_t E, const void* C, mp_precision p
   }
   p.n_dist = d + (mode == MP_MARGINALS_AND_TOTAL ? 1 : 0);
   for (int q = 0; q < p.n_dist; ++q) p.dist_src[q] = q < d ? q : -1;
-  const int64_t blocks = (E + 4 * kOccPerWave - 1) / (4 * kOccPerWave);
+  const bool row = short_runs(M, p.n_runs, elem_bytes_c(prec));
+  const int64_t per = 4 * kOccPerWave * (row ? 4 : 1);
+  const dim3 grid((unsigned)((E + per - 1) / per));
+  auto go = [&](auto kernel, auto* c) {
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, p, c, nq);
+  };
   if (prec == MP_FP64)
-    hipLaunchKernelGGL(occupations_kernel<double>, dim3((unsigned)blocks), dim3(256), 0, stream, p,
-                       (const double*)C, nq);
+    go(row ? occupations_kernel<double, 16> : occupations_kernel<double, 64>, (const double*)C);
   else
-    hipLaunchKernelGGL(occupations_kernel<float>, dim3((unsigned)blocks), dim3(256), 0, stream, p,
-                       (const float*)C, nq);
+    go(row ? occupations_kernel<float, 16> : occupations_kernel<float, 64>, (const float*)C);
   MP_HIP_LAUNCH_CHECK("mp_occupations launch");
   return MP_OK;
 }

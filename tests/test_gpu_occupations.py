@@ -1,0 +1,62 @@
+"""Per-sample occupations at the edges of their lane groups: a row of 16 lanes per
+sample (average runs up to 512 bytes) and a wave per sample (longer), runs that
+start off the 16-byte boundaries, modes that no bin counts, runs of one bin apart,
+and sample counts around a wave's share, against numpy.
+
+Tolerance: 2 (m + 4) u of a run set's sum of |products| (u = 2^-53), the bound of
+any order of FP64 products and sums over its m modes.  Modes outside the bins and
+the padding hold NaN, which must not reach a sum."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _bins(M, runs):
+    """runs: (lo, hi, bin); other modes are not counted."""
+    b = np.full(M, -1, np.int32)
+    for lo, hi, q in runs:
+        b[lo:hi] = q
+    return b
+
+
+CASES = [
+    (1, 1, [(0, 1, 0)]),
+    (20, 5, [(1, 16, 0), (17, 20, 1)]),
+    (40, 67, [(3, 20, 1), (20, 36, 0), (37, 39, 1)]),
+    (131, 64, [(1, 66, 0), (66, 131, 1)]),
+    (300, 17, [(0, 130, 0), (131, 195, 1), (195, 299, 2)]),
+    (259, 33, [(2, 259, 0)]),
+    (1100, 7, [(0, 258, 0), (259, 1099, 1)]),
+    (2305, 3, [(1, 2304, 0)]),
+    (90, 130, [(9 * i + 1, 9 * i + 9, i % 8) for i in range(10)]),
+]
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("mode", ["marginals", "marginals_and_total"])
+@pytest.mark.parametrize("M,E,runs", CASES)
+def test_occupations_of_runs(prec, mode, M, E, runs):
+    import torch
+
+    import paper_2503_12749_amd as mp
+    rng = np.random.default_rng(M + E)
+    dt = np.float64 if prec == "fp64" else np.float32
+    bins = _bins(M, runs)
+    d = int(bins.max()) + 1
+    ldm = mp.mp_ld_modes(M)
+    C = np.full((2 * E, 2, ldm), np.nan, dtype=dt)
+    C[:, :, :M] = rng.standard_normal((2 * E, 2, M)).astype(dt)
+    C[:, :, :M][:, :, bins < 0] = np.nan
+    n_dist = d + (mode == "marginals_and_total")
+    nq = torch.full((E * n_dist * 2,), 7.0, dtype=torch.float64, device="cuda")
+    mp.mp_occupations(M, E, torch.from_numpy(C.reshape(-1)).cuda(), prec, d, bins, mode, nq)
+    got = nq.cpu().numpy().reshape(E, n_dist, 2)
+    X = C[:, :, :M].astype(np.float64)
+    a, b, c, e = X[:E, 0], X[:E, 1], X[E:, 0], X[E:, 1]
+    for q in range(n_dist):
+        m = bins == q if q < d else bins >= 0
+        u = 2.0 * (m.sum() + 4) * 2.0 ** -53
+        for comp, x, y in ((0, a * c, b * e), (1, b * c, -a * e)):
+            tol = u * (np.abs(x) + np.abs(y))[:, m].sum(1)
+            assert np.all(np.abs(got[:, q, comp] - (x + y)[:, m].sum(1)) <= tol), (q, comp)
