@@ -301,10 +301,12 @@ __global__ __launch_bounds__(kCountThreads) void counts_fused(CountsParams p, Sr
           const d2 v = s_nb[i][q], c = s_c[i];
           // log-magnitudes of the two terms are xr + c1 and c2 - xr; a term
           // below e^kLogEps is skipped (a NaN one is kept: it must reach the sums)
-          const double xr = cm1 * v.x - sn * v.y;
+          // (fused in this order: partials of few bits reach rounding ties of the FP32 terms at
+          // theta = pi/2 and 3 pi/2)
+          const double xr = fma(cm1, v.x, -(sn * v.y));
           const bool t1 = !(xr + c.x <= kLogEps), t2 = c.y != -INFINITY && !(c.y - xr <= kLogEps);
           if (!(t1 || t2)) continue;
-          const double xi = cm1 * v.y + sn * v.x;
+          const double xi = fma(sn, v.x, cm1 * v.y);
           double tr, ti;
           if (t1) {
             cis_exp<F64>(xr + c.x, xi - thl, tr, ti);
@@ -492,8 +494,9 @@ __device__ inline Joint2Point joint2_point(int k, int K, int m_lo, bool in) {
 template <bool F64>
 __device__ inline void joint2_factor(const Joint2Point& q, double R, double I, double c,
                                      double sign, double& fr, double& fi) {
-  const double xr = q.cm1 * R - q.sn * I, xi = q.cm1 * I + q.sn * R;
-  cis_exp<F64>(sign * xr + c, sign * xi - q.thl, fr, fi);
+  // (fused in this order, see counts_fused)
+  const double xr = fma(q.cm1, R, -(q.sn * I)), xi = fma(q.cm1, I, q.sn * R);
+  cis_exp<F64>(fma(sign, xr, c), fma(sign, xi, -q.thl), fr, fi);
 }
 
 typedef __attribute__((ext_vector_type(4))) double f64x4;
