@@ -35,35 +35,46 @@ __device__ __attribute__((always_inline)) inline void zero(f32x16 (&accR)[2][2],
       }
 }
 
-// One slab: are, aim, bre, bim point at [kSlab][kTile] planes in LDS.
-__device__ __attribute__((always_inline)) inline void slab(const float* are, const float* aim,
-                                                            const float* bre, const float* bim,
-                                                            int wi, int wj, int lane,
-                                                            f32x16 (&accR)[2][2],
-                                                            f32x16 (&accI)[2][2]) {
+// One slab (are, aim, bre, bim point at [kSlab][kTile] planes in LDS), for the block
+// products that `mask` names: bit 4 t + 2 a + b for samples 2 t, 2 t + 1 and the wave's
+// 32 x 32 block (a, b).  The next samples' fragments are read ahead of the products.
+__device__ __attribute__((always_inline)) inline void slab_masked(
+    const float* are, const float* aim, const float* bre, const float* bim, int wi, int wj, int lane,
+    uint64_t mask, f32x16 (&accR)[2][2], f32x16 (&accI)[2][2]) {
   const int lr = lane & 31, lh = lane >> 5;
-#pragma unroll 4
+  const float* pa[2] = {are + lh * kTile + 64 * wi + lr, aim + lh * kTile + 64 * wi + lr};
+  const float* pb[2] = {bre + lh * kTile + 64 * wj + lr, bim + lh * kTile + 64 * wj + lr};
+  float x[2][2], y[2][2], nx[2][2], ny[2][2];
+  auto read = [&](int t, float(&u)[2][2], float(&v)[2][2]) {
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int a = 0; a < 2; ++a) {
+        u[c][a] = pa[c][2 * t * kTile + 32 * a];
+        v[c][a] = pb[c][2 * t * kTile + 32 * a];
+      }
+  };
+  read(0, x, y);
+#pragma unroll
   for (int t = 0; t < kSlab / 2; ++t) {
-    const int kk = 2 * t + lh;
-    float ar[2], ai[2], br[2], bi[2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a) {
-      ar[a] = are[kk * kTile + 64 * wi + 32 * a + lr];
-      ai[a] = aim[kk * kTile + 64 * wi + 32 * a + lr];
-    }
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      br[b] = bre[kk * kTile + 64 * wj + 32 * b + lr];
-      bi[b] = bim[kk * kTile + 64 * wj + 32 * b + lr];
-    }
+    if (t + 1 < kSlab / 2) read(t + 1, nx, ny);
+    const uint32_t m = (uint32_t)(mask >> (4 * t));
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        accR[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(ar[a], br[b], accR[a][b], 0, 0, 0);
-        accR[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(-ai[a], bi[b], accR[a][b], 0, 0, 0);
-        accI[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(ar[a], bi[b], accI[a][b], 0, 0, 0);
-        accI[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(ai[a], br[b], accI[a][b], 0, 0, 0);
+      for (int b = 0; b < 2; ++b)
+        if (m & (1u << (2 * a + b))) {
+          accR[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[0][a], y[0][b], accR[a][b], 0, 0, 0);
+          accI[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[0][a], y[1][b], accI[a][b], 0, 0, 0);
+          accR[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(-x[1][a], y[1][b], accR[a][b], 0, 0, 0);
+          accI[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[1][a], y[0][b], accI[a][b], 0, 0, 0);
+        }
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int a = 0; a < 2; ++a) {
+        x[c][a] = nx[c][a];
+        y[c][a] = ny[c][a];
       }
   }
 }
