@@ -81,45 +81,54 @@ __device__ __attribute__((always_inline)) inline void slab_masked(
 
 // Three-product form of one slab: P1 += Ar Br^T, P2 += Ai Bi^T,
 // P3 += (Ar + Ai)(Br + Bi)^T, so that Re = P1 - P2 and Im = P3 - P1 - P2.  The
-// next samples' fragments are read ahead of the products.
+// fragments of four samples are read ahead of the products, two samples' at a time
+// (ds_read2st64, whose offsets span the planes: no address arithmetic).
 __device__ __attribute__((always_inline)) inline void slab3(const float* are, const float* aim,
                                                              const float* bre, const float* bim,
                                                              int wi, int wj, int lane,
                                                              f32x16 (&p1)[2][2], f32x16 (&p2)[2][2],
                                                              f32x16 (&p3)[2][2]) {
   const int lr = lane & 31, lh = lane >> 5;
-  const float* pa[2] = {are + lh * kTile + 64 * wi + lr, aim + lh * kTile + 64 * wi + lr};
-  const float* pb[2] = {bre + lh * kTile + 64 * wj + lr, bim + lh * kTile + 64 * wj + lr};
-  float x[2][2], y[2][2], nx[2][2], ny[2][2];  // [re, im][block]
-  auto read = [&](int t, float(&u)[2][2], float(&v)[2][2]) {
+  int oa[2] = {lh * kTile + 64 * wi + lr, lh * kTile + 64 * wi + lr + 32};
+  int ob[2] = {lh * kTile + 64 * wj + lr, lh * kTile + 64 * wj + lr + 32};
 #pragma unroll
-    for (int c = 0; c < 2; ++c)
+  for (int a = 0; a < 2; ++a) asm("" : "+v"(oa[a]), "+v"(ob[a]));  // an address each
+  float x[2][2][2], y[2][2][2], nx[2][2][2], ny[2][2][2];  // [step][re, im][block]
+  auto read = [&](int t, float(&u)[2][2][2], float(&v)[2][2][2]) {
 #pragma unroll
-      for (int a = 0; a < 2; ++a) {
-        u[c][a] = pa[c][2 * t * kTile + 32 * a];
-        v[c][a] = pb[c][2 * t * kTile + 32 * a];
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        u[g][0][a] = are[oa[a] + 2 * (t + g) * kTile];
+        v[g][0][a] = bre[ob[a] + 2 * (t + g) * kTile];
+        u[g][1][a] = aim[oa[a] + 2 * (t + g) * kTile];
+        v[g][1][a] = bim[ob[a] + 2 * (t + g) * kTile];
       }
   };
   read(0, x, y);
 #pragma unroll
-  for (int t = 0; t < kSlab / 2; ++t) {
-    if (t + 1 < kSlab / 2) read(t + 1, nx, ny);
+  for (int t = 0; t < kSlab / 2; t += 2) {
+    if (t + 2 < kSlab / 2) read(t + 2, nx, ny);
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int g = 0; g < 2; ++g)
 #pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        p1[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[0][a], y[0][b], p1[a][b], 0, 0, 0);
-        p2[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[1][a], y[1][b], p2[a][b], 0, 0, 0);
-        p3[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[0][a] + x[1][a], y[0][b] + y[1][b],
-                                                        p3[a][b], 0, 0, 0);
-      }
+      for (int a = 0; a < 2; ++a)
 #pragma unroll
-    for (int c = 0; c < 2; ++c)
+        for (int b = 0; b < 2; ++b) {
+          p1[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[g][0][a], y[g][0][b], p1[a][b], 0, 0, 0);
+          p2[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[g][1][a], y[g][1][b], p2[a][b], 0, 0, 0);
+          p3[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(
+              x[g][0][a] + x[g][1][a], y[g][0][b] + y[g][1][b], p3[a][b], 0, 0, 0);
+        }
 #pragma unroll
-      for (int a = 0; a < 2; ++a) {
-        x[c][a] = nx[c][a];
-        y[c][a] = ny[c][a];
-      }
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+          x[g][c][a] = nx[g][c][a];
+          y[g][c][a] = ny[g][c][a];
+        }
   }
 }
 

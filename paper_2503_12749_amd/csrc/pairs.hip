@@ -60,11 +60,14 @@ __global__ __launch_bounds__(256) void mode_occupations_kernel(int64_t ldm, int6
   *(V*)(X + (E + k) * ldm + i) = b * c - a * e;
 }
 
+constexpr int64_t kXcds = 8;
+
 struct PairParams {
   int64_t M, ldm, E, e0, ns, s_first;
   int nb;           // mode blocks per side (ldm / tile)
   int n_pairs;      // nb (nb + 1) / 2
   int pieces;       // sample pieces per (tile, sub-ensemble) item
+  int64_t items;    // (sub-ensemble, piece, tile pair) items of the chunk
   int64_t piece;    // samples per piece (a multiple of the slab)
   float* part;      // pieces > 1: partial tiles [item][piece][128 x 128][re, im]
 };
@@ -82,11 +85,16 @@ __device__ inline void pair_of_index(int q, int nb, int& I, int& J) {
 
 // Workgroup -> (sub-ensemble, piece, tile pair) and the chunk-local sample
 // range [k0, k1) of that piece of the sub-ensemble (empty for pieces past a
-// short sub-ensemble's end).
-__device__ inline void pair_item(const PairParams& p, int& I, int& J, int64_t& s, int& pc,
+// short sub-ensemble's end); false for workgroups past the last.  Workgroups go to the
+// XCDs in turn: each takes an eighth of the items in one run, so the tile pairs of a
+// (sub-ensemble, piece) share one L2 instead of eight.
+__device__ inline bool pair_item(const PairParams& p, int& q, int& I, int& J, int64_t& s, int& pc,
                                  int64_t& k0, int64_t& k1) {
-  const int q = (int)(blockIdx.x % (unsigned)p.n_pairs);
-  const int64_t rest = blockIdx.x / (unsigned)p.n_pairs;
+  const int64_t per = (p.items + kXcds - 1) / kXcds;
+  const int64_t item = blockIdx.x % kXcds * per + blockIdx.x / kXcds;
+  if (item >= p.items) return false;
+  q = (int)(item % p.n_pairs);
+  const int64_t rest = item / p.n_pairs;
   pc = (int)(rest % p.pieces);
   s = p.s_first + rest / p.pieces;
   pair_of_index(q, p.nb, I, J);
@@ -95,6 +103,7 @@ __device__ inline void pair_item(const PairParams& p, int& I, int& J, int64_t& s
   const int64_t b = hi < p.E ? hi : p.E;
   k0 = a;
   k1 = a + p.piece < b ? a + p.piece : b;
+  return true;
 }
 
 // Partial tile of (sub-ensemble s, tile pair q, piece pc).
@@ -138,15 +147,18 @@ static_assert(PT == cmfma::kTile && PK == cmfma::kSlab, "tile shape of the share
 // (global_load_lds, whole 512-byte sample rows) into two stages, with one barrier
 // per slab: past it slab s has landed and every wave has read slab s - 1, whose
 // stage the loads of slab s + 1 refill.  Samples past the range repeat the last one
-// and are cleared in LDS in the last slab.  Bound by the FP32 matrix cores.  1e5
-// samples of M = 1000: 3.25 ms (MFMA time alone 2.25 ms) against 3.49 ms with slabs
-// staged through registers and two barriers around the LDS writes.
+// and are cleared in LDS in the last slab.  Bound by the FP32 matrix cores (75 %
+// busy; one wave per SIMD, so the loads' addresses and the barrier are not hidden).
+// 1e5 samples of M = 1000: 3.49 ms with slabs staged through registers and two
+// barriers around the LDS writes, 3.25 ms with direct loads, 3.03 ms with each XCD
+// on its own samples (pair_item) and no address arithmetic in the slab; the MFMA time
+// alone is 2.25 ms.
 __global__ __launch_bounds__(256, 1) void pair_corr_f32(PairParams p, const float* __restrict__ X,
                                                        double* __restrict__ acc) {
   __shared__ __attribute__((aligned(1024))) float lds[2][4][PK][PT];  // Re I, Im I, Re J, Im J
-  int I, J, pc;
+  int q, I, J, pc;
   int64_t s, k0, k1;
-  pair_item(p, I, J, s, pc, k0, k1);
+  if (!pair_item(p, q, I, J, s, pc, k0, k1)) return;
   const bool diag = I == J;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int wi = wave >> 1, wj = wave & 1;
@@ -156,11 +168,19 @@ __global__ __launch_bounds__(256, 1) void pair_corr_f32(PairParams p, const floa
   const float* src = X + (wave & 1 ? p.E * p.ldm : 0) + (wave < 2 ? I : J) * PT + 4 * (lane & 31);
   auto load = [&](int st, int64_t kb) {
     if (diag && wave >= 2) return;
+    if (kb + PK <= k1) {
+      const float* g = src + (kb + (lane >> 5)) * p.ldm;
 #pragma unroll
-    for (int q = 0; q < PK / 2; ++q) {
-      const int64_t k = kb + 2 * q + (lane >> 5);
-      __builtin_amdgcn_global_load_lds((const void*)(src + (k < k1 ? k : k1 - 1) * p.ldm),
-                                       (lds_void*)&lds[st][wave][2 * q][0], 16, 0, 0);
+      for (int r = 0; r < PK; r += 2)
+        __builtin_amdgcn_global_load_lds((const void*)(g + r * p.ldm),
+                                         (lds_void*)&lds[st][wave][r][0], 16, 0, 0);
+    } else {
+#pragma unroll
+      for (int r = 0; r < PK; r += 2) {
+        const int64_t k = kb + r + (lane >> 5);
+        __builtin_amdgcn_global_load_lds((const void*)(src + (k < k1 ? k : k1 - 1) * p.ldm),
+                                         (lds_void*)&lds[st][wave][r][0], 16, 0, 0);
+      }
     }
   };
   const int pj = diag ? 0 : 2;
@@ -203,7 +223,7 @@ __global__ __launch_bounds__(256, 1) void pair_corr_f32(PairParams p, const floa
 
   if (p.pieces > 1) {
     // partial tile, element (row, col) at 2 (128 row + col)
-    float* t = part_tile(p, s, (int)(blockIdx.x % (unsigned)p.n_pairs), pc);
+    float* t = part_tile(p, s, q, pc);
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
@@ -259,9 +279,9 @@ constexpr int QK = 16;  // samples per slab
 __global__ __launch_bounds__(256) void pair_corr_f64(PairParams p, const double* __restrict__ X,
                                                     double* __restrict__ acc) {
   __shared__ __attribute__((aligned(32))) double lds[4][QK][QT];
-  int I, J, pc;
+  int q, I, J, pc;
   int64_t s, k0, k1;
-  pair_item(p, I, J, s, pc, k0, k1);
+  if (!pair_item(p, q, I, J, s, pc, k0, k1)) return;
   const bool diag = I == J;
   const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
   const int lc = (tid & 15) * 4, lrow = tid >> 4;
@@ -384,7 +404,8 @@ mp_status pair_corr_launch(int32_t M, int64_t E, const void* X, mp_precision pre
   }
   p.part = (float*)ws;
   const int64_t n_touched = (e0 + E - 1) / ns - p.s_first + 1;
-  const int64_t blocks = n_touched * p.n_pairs * p.pieces;
+  p.items = n_touched * p.n_pairs * p.pieces;
+  const int64_t blocks = (p.items + kXcds - 1) / kXcds * kXcds;
   if (blocks > 0x7fffffff) {
     set_error("mp_pair_correlations_accumulate: %lld workgroups exceed the grid limit",
               (long long)blocks);
