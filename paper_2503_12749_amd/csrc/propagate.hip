@@ -106,34 +106,32 @@ __global__ void pack_transmission(const double* __restrict__ T, int M, int64_t l
 // ---------------------------------------------------------------- tile order
 
 // Tile order.  Blocks are dispatched to the XCDs round-robin, so block b
-// runs on XCD b % 8 and, with one workgroup per CU, the 32 blocks
-// b / 8 = 32 s .. 32 s + 31 of every XCD run together in "step" s.  In each
-// step all eight XCDs work on the same group of 8 row tiles, each XCD on its
-// own 4 column tiles, and consecutive steps move along the columns.  The A
-// rows of a group are then shared by every XCD through the infinity cache
-// (MALL) and fetched from HBM about once per group, instead of once per XCD
-// and column block (measured faster than XCD-local groups of 8 row tiles).
-constexpr int kStepRows = 8, kStepColsPerXcd = 4;
+// runs on XCD b % 8, and with one workgroup per CU 32 blocks of each XCD run
+// together.  All eight XCDs work on the same group of kStepRows row tiles (the last
+// group takes what is left), each XCD on every eighth column tile, rows first: four
+// columns of a full group at a time.  The A rows of a group are then shared by
+// every XCD through the infinity cache (MALL) and fetched from HBM about once per
+// group, instead of once per XCD and column block (measured faster than XCD-local
+// groups of 8 row tiles).  Only tiles of the product are numbered, but for the
+// up to seven columns that complete the last round of the XCDs: blocks without a tile
+// end at once, but leave the CUs that they were dealt to idle for the turn.  Numbered in
+// full groups of eight rows, products of fewer ran on that share of the CUs: FP32,
+// 1.2e5 samples of M = 86 (one row of tiles): 636 us, now 187 us; 6e4 of M = 310
+// (three): 692 us, now 520 us.
+constexpr int kStepRows = 8;
 
-// SR row tiles by SC column tiles per XCD and step (SR SC = 32 workgroups).
-template <int SR = kStepRows, int SC = kStepColsPerXcd>
 __device__ inline bool tile_of_block(int tiles_m, int tiles_n, int& tm, int& tn) {
-  const int b = blockIdx.x, x = b % kXcds, q = b / kXcds;
-  const int per_xcd = SR * SC;   // 32 blocks of one XCD per step
-  const int s = q / per_xcd, j = q % per_xcd;
-  const int cols_per_step = kXcds * SC;  // column tiles per step
-  const int n_cg = (tiles_n + cols_per_step - 1) / cols_per_step;
-  const int rg = s / n_cg, cg = s % n_cg;
-  tm = rg * SR + j % SR;
-  tn = cg * cols_per_step + x * SC + j / SR;
-  return tm < tiles_m && tn < tiles_n;
+  const int x = blockIdx.x % kXcds, q = blockIdx.x / kXcds;
+  const int per_xcd = (tiles_n + kXcds - 1) / kXcds;  // column tiles
+  const int rg = q / (kStepRows * per_xcd), j = q % (kStepRows * per_xcd);
+  const int rows = min(kStepRows, tiles_m - rg * kStepRows);
+  tm = rg * kStepRows + j % rows;
+  tn = j / rows * kXcds + x;
+  return tn < tiles_n;
 }
 
-template <int SR = kStepRows, int SC = kStepColsPerXcd>
-__host__ __device__ inline int mall_grid_blocks(int tiles_m, int tiles_n) {
-  const int n_cg = (tiles_n + kXcds * SC - 1) / (kXcds * SC);
-  const int n_rg = (tiles_m + SR - 1) / SR;
-  return n_rg * n_cg * kXcds * SR * SC;
+__host__ __device__ inline int tile_blocks(int tiles_m, int tiles_n) {
+  return tiles_m * ((tiles_n + kXcds - 1) / kXcds) * kXcds;
 }
 
 // ---------------------------------------------------------------- split, 256 x 256
@@ -1287,11 +1285,8 @@ __device__ __attribute__((always_inline)) inline void split1t_pp_tile(
 }
 
 // The L2 prefetch of the T-split kernels touches the sample operand's pairs
-// (M = 8000, fused call: 51.3 ms against 55.7 ms touching A's rows; with 4 x 8
-// tiles per XCD step 52.0 and 56.2 ms).
+// (M = 8000, fused call: 51.3 ms against 55.7 ms touching A's rows).
 constexpr bool kSplit1tPfA = false;
-// Tile order of the T-split kernels: row tiles by column tiles per XCD and step.
-constexpr int kS1tStepRows = 8, kS1tStepCols = 4;
 
 template <bool PF>
 __global__ __launch_bounds__(kThreads, 1) void gemm_split1t_pp(const uint16_t* __restrict__ A,
@@ -1302,7 +1297,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_split1t_pp(const uint16_t* _
   __shared__ __attribute__((aligned(1024))) uint16_t lds[kSplit1LdsElems];
   const int tiles_m = (int)(2 * ldm / S_BM), tiles_n = (int)((ncols + S_BN - 1) / S_BN);
   int tm, tn;
-  if (!tile_of_block<kS1tStepRows, kS1tStepCols>(tiles_m, tiles_n, tm, tn)) return;
+  if (!tile_of_block(tiles_m, tiles_n, tm, tn)) return;
   split1t_pp_tile<false, PF, kSplit1tPfA>(lds, A, B, C, ldm, ncols, kmodes, e_real, (int64_t)tm * S_BM,
                                           (int64_t)tn * S_BN, out_scale, nullptr);
 }
@@ -1315,7 +1310,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_split1t_occ(const uint16_t* 
   __shared__ __attribute__((aligned(1024))) uint16_t lds[kSplit1LdsElems];
   const int tiles_m = (int)(2 * ldm / S_BM), tiles_n = (int)((ncols + S_BN - 1) / S_BN);
   int tm, tn;
-  if (!tile_of_block<kS1tStepRows, kS1tStepCols>(tiles_m, tiles_n, tm, tn)) return;
+  if (!tile_of_block(tiles_m, tiles_n, tm, tn)) return;
   split1t_pp_tile<true, PF, kSplit1tPfA>(lds, A, B, nullptr, ldm, ncols, kmodes, 0, (int64_t)tm * 128,
                                          (int64_t)tn * 128, out_scale, &fo);
 }
@@ -1674,7 +1669,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_split1t8_pp(const uint16_t* 
   __shared__ __attribute__((aligned(1024))) char lds[F8_LDS];
   const int tiles_m = (int)(2 * ldm / S_BM), tiles_n = (int)((ncols + S_BN - 1) / S_BN);
   int tm, tn;
-  if (!tile_of_block<kS1tStepRows, kS1tStepCols>(tiles_m, tiles_n, tm, tn)) return;
+  if (!tile_of_block(tiles_m, tiles_n, tm, tn)) return;
   const uint8_t* A8 = (const uint8_t*)A + 4 * ldm * ldm;
   const uint8_t* B8 = (const uint8_t*)B + 2 * ncols * ldm;
   split1t8_pp_tile<0, PF>(lds, A, A8, B, B8, C, ldm, ncols, kmodes, e_real, (int64_t)tm * S_BM,
@@ -1690,7 +1685,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_split1t8_occ(const uint16_t*
   __shared__ __attribute__((aligned(1024))) char lds[F8_LDS];
   const int tiles_m = (int)(2 * ldm / S_BM), tiles_n = (int)((ncols + S_BN - 1) / S_BN);
   int tm, tn;
-  if (!tile_of_block<kS1tStepRows, kS1tStepCols>(tiles_m, tiles_n, tm, tn)) return;
+  if (!tile_of_block(tiles_m, tiles_n, tm, tn)) return;
   const uint8_t* A8 = (const uint8_t*)A + 4 * ldm * ldm;
   const uint8_t* B8 = (const uint8_t*)B + 2 * ncols * ldm;
   split1t8_pp_tile<1, PF>(lds, A, A8, B, B8, nullptr, ldm, ncols, kmodes, 0, (int64_t)tm * 128,
@@ -1708,7 +1703,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_split1t8_bilin(
   __shared__ __attribute__((aligned(1024))) char lds[F8_LDS];
   const int tiles_m = (int)(2 * ldm / S_BM), tiles_n = (int)((ncols + S_BN - 1) / S_BN);
   int tm, tn;
-  if (!tile_of_block<kS1tStepRows, kS1tStepCols>(tiles_m, tiles_n, tm, tn)) return;
+  if (!tile_of_block(tiles_m, tiles_n, tm, tn)) return;
   const uint8_t* A8 = (const uint8_t*)A + 4 * ldm * ldm;
   split1t8_pp_tile<2, PF>(lds, A, A8, B, B8, nullptr, ldm, ncols, kmodes, 0, (int64_t)tm * 128,
                           (int64_t)tn * S_BN, out_scale, scale_a, &fo, -1, alpha, diag);
@@ -2064,11 +2059,7 @@ size_t propagate_workspace(int32_t M, mp_precision prec) {
 int k_modes(int32_t M, int depth) { return (M + depth - 1) / depth * depth; }
 
 static int grid_tiles(int64_t ldm, int64_t ncols, int bm, int bn) {
-  return mall_grid_blocks((int)(2 * ldm / bm), (int)((ncols + bn - 1) / bn));
-}
-static int grid_tiles_s1t(int64_t ldm, int64_t ncols) {
-  return mall_grid_blocks<kS1tStepRows, kS1tStepCols>((int)(2 * ldm / S_BM),
-                                                       (int)((ncols + S_BN - 1) / S_BN));
+  return tile_blocks((int)(2 * ldm / bm), (int)((ncols + bn - 1) / bn));
 }
 
 // Power-of-two prescale of T for the FP16 split operand: |T_ij| ~ M^-1/2 for
@@ -2173,7 +2164,7 @@ mp_status gemm_packed_launch(int32_t M, int64_t E, const void* packed, mp_precis
       // tiles over the storage columns (2 E2), stored to C columns
       const int64_t scols = 2 * split1t_half(E);
       auto kernel = split_prefetch_for(ldm) ? gemm_split1t_pp<true> : gemm_split1t_pp<false>;
-      hipLaunchKernelGGL(kernel, dim3(grid_tiles_s1t(ldm, scols)), dim3(kThreads), 0, stream,
+      hipLaunchKernelGGL(kernel, dim3(grid_tiles(ldm, scols, S_BM, S_BN)), dim3(kThreads), 0, stream,
                          (const uint16_t*)packed, (const uint16_t*)ab, (float*)C, ldm, scols, k_modes(M), E,
                          ldexpf(1.0f, -fp16_scale_exp(M)));
       break;
@@ -2181,7 +2172,7 @@ mp_status gemm_packed_launch(int32_t M, int64_t E, const void* packed, mp_precis
     case MP_SPLIT1T_F8: {
       const int64_t scols = 2 * split1t_half(E);
       auto kernel = split_prefetch_for(ldm) ? gemm_split1t8_pp<true> : gemm_split1t8_pp<false>;
-      hipLaunchKernelGGL(kernel, dim3(grid_tiles_s1t(ldm, scols)), dim3(kThreads), 0, stream,
+      hipLaunchKernelGGL(kernel, dim3(grid_tiles(ldm, scols, S_BM, S_BN)), dim3(kThreads), 0, stream,
                          (const uint16_t*)packed, (const uint16_t*)ab, (float*)C, ldm, scols, k_modes(M), E,
                          ldexpf(1.0f, -fp16_scale_exp(M)), f8_scale_a(M));
       break;
@@ -2256,7 +2247,7 @@ mp_status gemm_fused_launch(int32_t M, int64_t E, const void* packed, mp_precisi
     case MP_SPLIT1T_FP16: {
       const int64_t scols = 2 * split1t_half(E);  // storage columns, beta from E2 on
       auto kernel = split_prefetch_for(ldm) ? gemm_split1t_occ<true> : gemm_split1t_occ<false>;
-      hipLaunchKernelGGL(kernel, dim3(grid_tiles_s1t(ldm, scols)), dim3(kThreads), 0, stream,
+      hipLaunchKernelGGL(kernel, dim3(grid_tiles(ldm, scols, S_BM, S_BN)), dim3(kThreads), 0, stream,
                          (const uint16_t*)packed, (const uint16_t*)ab, ldm, scols, k_modes(M),
                          ldexpf(1.0f, -fp16_scale_exp(M)), fo);
       break;
@@ -2264,7 +2255,7 @@ mp_status gemm_fused_launch(int32_t M, int64_t E, const void* packed, mp_precisi
     case MP_SPLIT1T_F8: {
       const int64_t scols = 2 * split1t_half(E);
       auto kernel = split_prefetch_for(ldm) ? gemm_split1t8_occ<true> : gemm_split1t8_occ<false>;
-      hipLaunchKernelGGL(kernel, dim3(grid_tiles_s1t(ldm, scols)), dim3(kThreads), 0, stream,
+      hipLaunchKernelGGL(kernel, dim3(grid_tiles(ldm, scols, S_BM, S_BN)), dim3(kThreads), 0, stream,
                          (const uint16_t*)packed, (const uint16_t*)ab, ldm, scols, k_modes(M),
                          ldexpf(1.0f, -fp16_scale_exp(M)), f8_scale_a(M), fo);
       break;
@@ -2346,7 +2337,7 @@ mp_status gemm_bilinear_launch(int32_t M, int64_t E, const void* packed, mp_prec
   const uint8_t* B8 = (const uint8_t*)ab + 4 * e2 * ldm + e2 * ldm;  // their e4m3 copies
   auto kernel = split_prefetch_for(ldm) ? gemm_split1t8_bilin<true> : gemm_split1t8_bilin<false>;
   const float* diag = (const float*)((const char*)packed + propagate_workspace(M, prec));
-  hipLaunchKernelGGL(kernel, dim3(grid_tiles_s1t(ldm, e2)), dim3(kThreads), 0, stream,
+  hipLaunchKernelGGL(kernel, dim3(grid_tiles(ldm, e2, S_BM, S_BN)), dim3(kThreads), 0, stream,
                      (const uint16_t*)packed, B, B8, alpha, diag, ldm, e2, k_modes(M),
                      ldexpf(1.0f, -fp16_scale_exp(M)), f8_scale_a(M), fo);
   MP_HIP_LAUNCH_CHECK("mp_propagate_counts_bilinear gemm launch");
