@@ -36,6 +36,7 @@ typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
 constexpr int kThreads = 256;
+constexpr int kCus = 256;   // workgroups of a persistent launch (a multiple of kXcds)
 constexpr int kXcds = 8;     // MI355X: 8 XCDs, workgroups dispatched round-robin
 
 // ---------------------------------------------------------------- packing
@@ -120,8 +121,8 @@ __global__ void pack_transmission(const double* __restrict__ T, int M, int64_t l
 // (three): 692 us, now 520 us.
 constexpr int kStepRows = 8;
 
-__device__ inline bool tile_of_block(int tiles_m, int tiles_n, int& tm, int& tn) {
-  const int x = blockIdx.x % kXcds, q = blockIdx.x / kXcds;
+__device__ inline bool tile_of_block(int b, int tiles_m, int tiles_n, int& tm, int& tn) {
+  const int x = b % kXcds, q = b / kXcds;
   const int per_xcd = (tiles_n + kXcds - 1) / kXcds;  // column tiles
   const int rg = q / (kStepRows * per_xcd), j = q % (kStepRows * per_xcd);
   const int rows = min(kStepRows, tiles_m - rg * kStepRows);
@@ -247,7 +248,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_f64_pp(const double* __restr
   __shared__ __attribute__((aligned(1024))) double lds[D_NST][D_ROWS * D_BK];
   const int tiles_m = (int)(2 * ldm / D_BM), tiles_n = (int)((ncols + D_BN - 1) / D_BN);
   int tm, tn;
-  if (!tile_of_block(tiles_m, tiles_n, tm, tn)) return;
+  if (!tile_of_block(blockIdx.x, tiles_m, tiles_n, tm, tn)) return;
   const int64_t m0 = (int64_t)tm * D_BM, n0 = (int64_t)tn * D_BN;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int wm = wave >> 1, wn = wave & 1;
@@ -744,7 +745,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_split_256_pp(const uint16_t*
   uint16_t (*lds)[4][S_PLANE] = (uint16_t (*)[4][S_PLANE])lds_raw;
   const int tiles_m = (int)(2 * ldm / S_BM), tiles_n = (int)((ncols + S_BN - 1) / S_BN);
   int tm, tn;
-  if (!tile_of_block(tiles_m, tiles_n, tm, tn)) return;
+  if (!tile_of_block(blockIdx.x, tiles_m, tiles_n, tm, tn)) return;
   split_pp_tile<H, false, PF>(lds, A, B, C, ldm, ncols, kmodes, (int64_t)tm * S_BM, (int64_t)tn * S_BN,
                               out_scale, nullptr);
 }
@@ -760,7 +761,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_split_occ(const uint16_t* __
   uint16_t (*lds)[4][S_PLANE] = (uint16_t (*)[4][S_PLANE])lds_raw;
   const int tiles_m = (int)(2 * ldm / S_BM), tiles_n = (int)((ncols + S_BN - 1) / S_BN);
   int tm, tn;
-  if (!tile_of_block(tiles_m, tiles_n, tm, tn)) return;
+  if (!tile_of_block(blockIdx.x, tiles_m, tiles_n, tm, tn)) return;
   split_pp_tile<H, true, PF>(lds, A, B, nullptr, ldm, ncols, kmodes, (int64_t)tm * 128, (int64_t)tn * 128,
                              out_scale, &fo);
 }
@@ -1042,7 +1043,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_split1_pp(const uint16_t* __
   __shared__ __attribute__((aligned(1024))) uint16_t lds[kSplit1LdsElems];
   const int tiles_m = (int)(2 * ldm / S_BM), tiles_n = (int)((ncols + S_BN - 1) / S_BN);
   int tm, tn;
-  if (!tile_of_block(tiles_m, tiles_n, tm, tn)) return;
+  if (!tile_of_block(blockIdx.x, tiles_m, tiles_n, tm, tn)) return;
   split1_pp_tile<false, PF>(lds, A, B, C, ldm, ncols, kmodes, (int64_t)tm * S_BM, (int64_t)tn * S_BN,
                             out_scale, nullptr);
 }
@@ -1055,7 +1056,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_split1_occ(const uint16_t* _
   __shared__ __attribute__((aligned(1024))) uint16_t lds[kSplit1LdsElems];
   const int tiles_m = (int)(2 * ldm / S_BM), tiles_n = (int)((ncols + S_BN - 1) / S_BN);
   int tm, tn;
-  if (!tile_of_block(tiles_m, tiles_n, tm, tn)) return;
+  if (!tile_of_block(blockIdx.x, tiles_m, tiles_n, tm, tn)) return;
   split1_pp_tile<true, PF>(lds, A, B, nullptr, ldm, ncols, kmodes, (int64_t)tm * 128, (int64_t)tn * 128,
                            out_scale, &fo);
 }
@@ -1297,7 +1298,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_split1t_pp(const uint16_t* _
   __shared__ __attribute__((aligned(1024))) uint16_t lds[kSplit1LdsElems];
   const int tiles_m = (int)(2 * ldm / S_BM), tiles_n = (int)((ncols + S_BN - 1) / S_BN);
   int tm, tn;
-  if (!tile_of_block(tiles_m, tiles_n, tm, tn)) return;
+  if (!tile_of_block(blockIdx.x, tiles_m, tiles_n, tm, tn)) return;
   split1t_pp_tile<false, PF, kSplit1tPfA>(lds, A, B, C, ldm, ncols, kmodes, e_real, (int64_t)tm * S_BM,
                                           (int64_t)tn * S_BN, out_scale, nullptr);
 }
@@ -1310,7 +1311,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_split1t_occ(const uint16_t* 
   __shared__ __attribute__((aligned(1024))) uint16_t lds[kSplit1LdsElems];
   const int tiles_m = (int)(2 * ldm / S_BM), tiles_n = (int)((ncols + S_BN - 1) / S_BN);
   int tm, tn;
-  if (!tile_of_block(tiles_m, tiles_n, tm, tn)) return;
+  if (!tile_of_block(blockIdx.x, tiles_m, tiles_n, tm, tn)) return;
   split1t_pp_tile<true, PF, kSplit1tPfA>(lds, A, B, nullptr, ldm, ncols, kmodes, 0, (int64_t)tm * 128,
                                          (int64_t)tn * 128, out_scale, &fo);
 }
@@ -1669,7 +1670,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_split1t8_pp(const uint16_t* 
   __shared__ __attribute__((aligned(1024))) char lds[F8_LDS];
   const int tiles_m = (int)(2 * ldm / S_BM), tiles_n = (int)((ncols + S_BN - 1) / S_BN);
   int tm, tn;
-  if (!tile_of_block(tiles_m, tiles_n, tm, tn)) return;
+  if (!tile_of_block(blockIdx.x, tiles_m, tiles_n, tm, tn)) return;
   const uint8_t* A8 = (const uint8_t*)A + 4 * ldm * ldm;
   const uint8_t* B8 = (const uint8_t*)B + 2 * ncols * ldm;
   split1t8_pp_tile<0, PF>(lds, A, A8, B, B8, C, ldm, ncols, kmodes, e_real, (int64_t)tm * S_BM,
@@ -1685,7 +1686,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_split1t8_occ(const uint16_t*
   __shared__ __attribute__((aligned(1024))) char lds[F8_LDS];
   const int tiles_m = (int)(2 * ldm / S_BM), tiles_n = (int)((ncols + S_BN - 1) / S_BN);
   int tm, tn;
-  if (!tile_of_block(tiles_m, tiles_n, tm, tn)) return;
+  if (!tile_of_block(blockIdx.x, tiles_m, tiles_n, tm, tn)) return;
   const uint8_t* A8 = (const uint8_t*)A + 4 * ldm * ldm;
   const uint8_t* B8 = (const uint8_t*)B + 2 * ncols * ldm;
   split1t8_pp_tile<1, PF>(lds, A, A8, B, B8, nullptr, ldm, ncols, kmodes, 0, (int64_t)tm * 128,
@@ -1703,7 +1704,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_split1t8_bilin(
   __shared__ __attribute__((aligned(1024))) char lds[F8_LDS];
   const int tiles_m = (int)(2 * ldm / S_BM), tiles_n = (int)((ncols + S_BN - 1) / S_BN);
   int tm, tn;
-  if (!tile_of_block(tiles_m, tiles_n, tm, tn)) return;
+  if (!tile_of_block(blockIdx.x, tiles_m, tiles_n, tm, tn)) return;
   const uint8_t* A8 = (const uint8_t*)A + 4 * ldm * ldm;
   split1t8_pp_tile<2, PF>(lds, A, A8, B, B8, nullptr, ldm, ncols, kmodes, 0, (int64_t)tm * 128,
                           (int64_t)tn * S_BN, out_scale, scale_a, &fo, -1, alpha, diag);
@@ -1777,6 +1778,16 @@ constexpr int F_PLANE = S_BM * F_BK;  // floats of one LDS operand plane
 // FUSED: tile (tm, tn) covers modes [128 tm, 128 tm + 128) and samples
 // [128 tn, 128 tn + 128) as in gemm_split_occ, and the epilogue is
 // fused_epilogue.
+// Otherwise the launch is persistent: a workgroup takes the tiles of blocks b,
+// b + gridDim.x, ... (gridDim.x is a multiple of 8, so they stay on its XCD), and
+// the slabs of its tiles are one stream: the last two slabs of a tile load the first
+// two of the next, so neither the start of a workgroup nor the first loads of a tile
+// leave the matrix cores idle, and C is written while the next tile is multiplied.
+// Load addresses are a scalar base and 32-bit lane offsets that are the same for every
+// tile.  Bound by the FP32 matrix cores (94 % busy within the waves).  1e5 samples of
+// M = 1000: 5.96 ms, 6.13 ms with a workgroup per tile; 4e4 of M = 512: 630 and 648 us;
+// 1.2e5 of M = 86: 175 and 184 us.  With addresses formed at each load the
+// persistent form gained nothing (6.15 ms).
 template <bool FUSED>
 __global__ __launch_bounds__(kThreads, 1) void gemm_f32_pp(const float* __restrict__ A,
                                                            const float* __restrict__ B,
@@ -1784,37 +1795,48 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_f32_pp(const float* __restri
                                                            int64_t ncols, int kmodes, FusedOut fo) {
   __shared__ __attribute__((aligned(1024))) float lds[2][2][F_PLANE];
   const int tiles_m = (int)(2 * ldm / S_BM), tiles_n = (int)((ncols + S_BN - 1) / S_BN);
-  int tm, tn;
-  if (!tile_of_block(tiles_m, tiles_n, tm, tn)) return;
-  const int64_t m0 = (int64_t)tm * (FUSED ? 128 : S_BM), n0 = (int64_t)tn * (FUSED ? 128 : S_BN);
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int blocks = tile_blocks(tiles_m, tiles_n);
+  int blk = blockIdx.x, tm, tn;
+  // the next block at or after blk with a tile; false past the last
+  auto next_tile = [&]() {
+    while (blk < blocks && !tile_of_block(blk, tiles_m, tiles_n, tm, tn)) blk += gridDim.x;
+    return blk < blocks;
+  };
+  if (!next_tile()) return;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int wm = wave >> 1, wn = wave & 1;
   const int lr = lane & 31, lh = lane >> 5;
 
   const int op = wave >> 1, half = wave & 1;
-  const float* src = op == 0 ? A + m0 * ldm : B + n0 * ldm;
-  // fused tiles: the second half of the rows are the Im rows (A) or the beta
-  // columns (B), and sample offsets past the chunk are clamped
-  const int64_t row_limit = op == 0 ? (FUSED ? 128 : S_BM) : (FUSED ? ncols / 2 - n0 : ncols - n0);
-  const int64_t hi_off = op == 0 ? ldm : ncols / 2;
   const int lrow = lane >> 3;
-  // lane l writes LDS slot 16 l of each 1 KB block (8 rows): row 8 q + l / 8
-  // of the wave's half, slot l % 8, which holds global chunk (l % 8) ^ swz8(row)
-  auto issue = [&](int st, int64_t k0) {
+  // first column that a tile loads: a ragged last tile takes the last 256 columns and
+  // stores its own, so the rows below are the same for every tile
+  auto load_col = [&](int64_t n) { return FUSED ? n : max((int64_t)0, min(n, ncols - S_BN)); };
+  // operand rows of tile (tm, tn) that this wave loads; fused tiles' second half of the
+  // rows are the Im rows (A) or the beta columns (B)
+  auto tile_src = [&]() {
+    const int64_t row = op == 0 ? (int64_t)tm * (FUSED ? 128 : S_BM)
+                                : load_col((int64_t)tn * (FUSED ? 128 : S_BN));
+    const int64_t upper = op == 0 ? ldm : ncols / 2;
+    return (op == 0 ? A : B) + (row + (FUSED && half ? upper : 0)) * ldm;
+  };
+  // lane l writes LDS slot 16 l of each 1 KB block (8 rows): row 8 q + l / 8 of the
+  // wave's half, slot l % 8, which holds global chunk (l % 8) ^ swz8(row).  Rows past
+  // the operand's last are clamped to it
+  const int64_t left = op == 0 ? S_BM : (FUSED ? ncols / 2 - (int64_t)tn * 128 : ncols);
+  uint32_t off[16];  // in bytes
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const int r = (FUSED ? 0 : half * 128) + 8 * q + lrow;
+    const int64_t row = r < left ? r : left - 1;
+    off[q] = (uint32_t)(4 * (row * ldm + (((lane & 7) ^ swz8(r)) << 2)));
+  }
+  auto issue = [&](int st, const float* src, int k0) {
     char* dst = (char*)&lds[st][op][0] + half * (128 * F_BK * 4);
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const int r = half * 128 + 8 * q + lrow;
-      int64_t row;
-      if constexpr (FUSED) {
-        const int64_t rr = 8 * q + lrow;  // row within the half
-        row = (rr < row_limit ? rr : row_limit - 1) + (half ? hi_off : 0);
-      } else {
-        row = r < row_limit ? r : row_limit - 1;
-      }
-      const float* g = src + row * ldm + k0 + (((lane & 7) ^ swz8(r)) << 2);
-      __builtin_amdgcn_global_load_lds((const void*)g, (lds_void*)(dst + q * 1024), 16, 0, 0);
-    }
+    for (int q = 0; q < 16; ++q)
+      __builtin_amdgcn_global_load_lds((const void*)((const char*)(src + k0) + off[q]),
+                                       (lds_void*)(dst + q * 1024), 16, 0, 0);
   };
   int oa[2][2][4], ob[2][2][4];
 #pragma unroll
@@ -1848,70 +1870,105 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_f32_pp(const float* __restri
       }
   };
 
-  f32x16 acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  const int KT = kmodes / F_BK;  // >= 2
-  issue(0, 0);
+  const int KT = kmodes / F_BK;  // even, >= 2
+  const float* src = tile_src();
+  issue(0, src, 0);
+  issue(1, src, F_BK);
   wait_vm<0>();
   barrier_no_fence();
-  issue(1, F_BK);
   read0(0);
   constexpr int kSgMfma = 0x008, kSgDsRead = 0x100, kSgVmem = 0x020;
-  for (int kt = 0; kt < KT; ++kt) {
-    const int cur = kt & 1;
-    // phase A: set 0 (steps 0-7) with the reads of set 1 threaded between them
-    read1(cur);
+  f32x16 acc[4][4];
+  int64_t m0, n0;
+  bool more;
+  do {
+    m0 = (int64_t)tm * (FUSED ? 128 : S_BM), n0 = (int64_t)tn * (FUSED ? 128 : S_BN);
+    // the tile after this one, whose first two slabs follow this one's (without one
+    // this tile's first slabs are loaded again, in bounds, and not used)
+    const float* nsrc = src;
+    blk += gridDim.x;
+    more = !FUSED && next_tile();
+    if (more) nsrc = tile_src();
 #pragma unroll
-    for (int s = 0; s < 8; ++s)
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int j = 0; j < 4; ++j)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0[s >> 2][i][s & 3], b0[s >> 2][j][s & 3],
-                                                           acc[i][j], 0, 0, 0);
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    for (int kt = 0; kt < KT; ++kt) {
+      const int cur = kt & 1;
+      // phase A: set 0 (steps 0-7) with the reads of set 1 threaded between them
+      read1(cur);
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      __builtin_amdgcn_sched_group_barrier(kSgMfma, 4, 0);
-      __builtin_amdgcn_sched_group_barrier(kSgDsRead, 1, 0);
+      for (int s = 0; s < 8; ++s)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0[s >> 2][i][s & 3], b0[s >> 2][j][s & 3],
+                                                             acc[i][j], 0, 0, 0);
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        __builtin_amdgcn_sched_group_barrier(kSgMfma, 4, 0);
+        __builtin_amdgcn_sched_group_barrier(kSgDsRead, 1, 0);
+      }
+      __builtin_amdgcn_sched_group_barrier(kSgMfma, 64, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      // own loads of slab kt + 1 landed (a tile's first slabs have before its loop, and
+      // the stores of the tile before may still be under way), reads of stage cur done
+      // (the branch is in the asm because one in the loop made the compiler copy the
+      // accumulators)
+      asm volatile(
+          "s_cmp_eq_u32 %0, 0\n\ts_cbranch_scc1 1f\n\ts_waitcnt vmcnt(0)\n1:\n\ts_waitcnt lgkmcnt(0)" ::"s"(kt)
+          : "scc", "memory");
+      barrier_no_fence();
+      __builtin_amdgcn_sched_barrier(0);
+      // phase B: set 1 (steps 8-15) with the loads of slab kt + 2 and the reads of
+      // set 0 of slab kt + 1 threaded in
+      const bool own = kt + 2 < KT;
+      issue(cur, own ? src : nsrc, (own ? kt + 2 : kt + 2 - KT) * F_BK);
+      read0(cur ^ 1);
+#pragma unroll
+      for (int s = 0; s < 8; ++s)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[s >> 2][i][s & 3], b1[s >> 2][j][s & 3],
+                                                             acc[i][j], 0, 0, 0);
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        __builtin_amdgcn_sched_group_barrier(kSgMfma, 2, 1);
+        __builtin_amdgcn_sched_group_barrier(kSgVmem, 1, 1);
+      }
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        __builtin_amdgcn_sched_group_barrier(kSgMfma, 4, 1);
+        __builtin_amdgcn_sched_group_barrier(kSgDsRead, 1, 1);
+      }
+      __builtin_amdgcn_sched_group_barrier(kSgMfma, 32, 1);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    __builtin_amdgcn_sched_group_barrier(kSgMfma, 64, 0);
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt(0);  // own loads of slab kt + 1 landed, reads of stage cur done
-    barrier_no_fence();
-    __builtin_amdgcn_sched_barrier(0);
-    // phase B: set 1 (steps 8-15) with the loads of slab kt + 2 and the reads
-    // of set 0 of slab kt + 1 threaded in (the last two slabs repeat the final
-    // slab into the freed stage, in bounds, so the loop has no branches)
-    issue(cur, (int64_t)min(kt + 2, KT - 1) * F_BK);
-    read0(cur ^ 1);
+    wait_vm<0>();  // the next tile's second slab landed
+    if constexpr (!FUSED) {
+      const int64_t ldc = 2 * ldm;
 #pragma unroll
-    for (int s = 0; s < 8; ++s)
+      for (int j = 0; j < 4; ++j) {
+        const int64_t col = load_col(n0) + wn * 128 + j * 32 + lr;
+        if (col >= n0 && col < ncols) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+          for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[s >> 2][i][s & 3], b1[s >> 2][j][s & 3],
-                                                           acc[i][j], 0, 0, 0);
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      __builtin_amdgcn_sched_group_barrier(kSgMfma, 2, 1);
-      __builtin_amdgcn_sched_group_barrier(kSgVmem, 1, 1);
+            for (int g = 0; g < 4; ++g) {
+              const int64_t row = m0 + wm * 128 + i * 32 + 8 * g + 4 * lh;
+              *(f32x4*)(C + col * ldc + row) = f32x4{acc[i][j][4 * g], acc[i][j][4 * g + 1],
+                                                     acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
+            }
+        }
+      }
+      src = nsrc;
     }
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      __builtin_amdgcn_sched_group_barrier(kSgMfma, 4, 1);
-      __builtin_amdgcn_sched_group_barrier(kSgDsRead, 1, 1);
-    }
-    __builtin_amdgcn_sched_group_barrier(kSgMfma, 32, 1);
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  __builtin_amdgcn_s_waitcnt(0);  // the repeated tail loads land before the wave ends
+  } while (more);
   if constexpr (FUSED) {
     // a unit scale the compiler cannot fold: with the constant 1 it kept the
     // accumulators for the stores of the beta waves in their registers and
@@ -1919,21 +1976,6 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_f32_pp(const float* __restri
     float one = 1.0f;
     asm volatile("" : "+s"(one));
     fused_epilogue(acc, &lds[0][0][0], fo, m0, n0, wm, wn, lane, one);
-    return;
-  }
-  const int64_t ldc = 2 * ldm;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int64_t col = n0 + wn * 128 + j * 32 + lr;
-    if (col >= ncols) continue;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int64_t row = m0 + wm * 128 + i * 32 + 8 * g + 4 * lh;
-        *(f32x4*)(C + col * ldc + row) =
-            f32x4{acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
-      }
   }
 }
 
@@ -2141,7 +2183,7 @@ mp_status gemm_packed_launch(int32_t M, int64_t E, const void* packed, mp_precis
                          stream, (const double*)packed, (const double*)ab, (double*)C, ldm, ncols, k_modes(M, D_BK));
       break;
     case MP_FP32:
-      hipLaunchKernelGGL(gemm_f32_pp<false>, dim3(grid_tiles(ldm, ncols, S_BM, S_BN)),
+      hipLaunchKernelGGL(gemm_f32_pp<false>, dim3(min(grid_tiles(ldm, ncols, S_BM, S_BN), kCus)),
                          dim3(kThreads), 0, stream, (const float*)packed, (const float*)ab,
                          (float*)C, ldm, ncols, k_modes(M), FusedOut{});
       break;

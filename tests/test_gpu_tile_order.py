@@ -32,3 +32,25 @@ def test_every_tile_once(prec, M, E):
     rows = np.linalg.norm(T, axis=1)
     for x, got, want in ((a, ga, a @ T.T), (b, gb, b @ T.conj().T)):
         assert np.all(np.abs(got - want) <= u * np.linalg.norm(x, axis=1)[:, None] * rows)
+
+
+@pytest.mark.parametrize("M,E", [(20, 32897), (70, 40000), (300, 22100)])
+def test_tiles_past_the_first_turn(M, E):
+    """More tiles than the persistent FP32 launch has workgroups, with ragged last columns:
+    two to ten slabs per tile.  Tolerance as above."""
+    import torch
+
+    import paper_2503_12749_amd as mp
+    rng = np.random.default_rng(M)
+    T = (rng.standard_normal((M, M)) + 1j * rng.standard_normal((M, M))) / np.sqrt(2 * M)
+    p = mp.CountsPipeline(T, np.linspace(0.4, 0.9, M), prec="fp32", seed=3, bin_of_mode=np.zeros(M, np.int32),
+                          d=1, mode="joint", windows=[(0, 8)], n_sub=1, samples_per_sub=E, chunk=E)
+    p.C.fill_(255)  # NaN
+    p.run_chunk(0, E)
+    torch.cuda.synchronize()
+    a, b = p.alpha_beta(E)
+    ga, gb = p.propagated(E)
+    u = 2 * (M + 4) * 2.0 ** -24
+    rows = np.linalg.norm(T, axis=1)
+    for x, got, want in ((a, ga, a @ T.T), (b, gb, b @ T.conj().T)):
+        assert np.all(np.abs(got - want) <= u * np.linalg.norm(x, axis=1)[:, None] * rows)
