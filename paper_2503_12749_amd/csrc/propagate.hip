@@ -250,7 +250,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_f64_pp(const double* __restr
   int tm, tn;
   if (!tile_of_block(blockIdx.x, tiles_m, tiles_n, tm, tn)) return;
   const int64_t m0 = (int64_t)tm * D_BM, n0 = (int64_t)tn * D_BN;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int wm = wave >> 1, wn = wave & 1;
   const int lr = lane & 15, lh = lane >> 4;
 
