@@ -735,7 +735,8 @@ __device__ __attribute__((always_inline)) inline void split_pp_tile(uint16_t (*l
   }
 }
 
-template <typename H, bool PF>
+// NJ = 2: the 256 x 128 tile (narrow_tiles).
+template <typename H, bool PF, int NJ>
 __global__ __launch_bounds__(kThreads, 1) void gemm_split_256_pp(const uint16_t* __restrict__ A,
                                                                  const uint16_t* __restrict__ B,
                                                                  float* __restrict__ C,
@@ -743,27 +744,29 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_split_256_pp(const uint16_t*
                                                                  float out_scale) {
   __shared__ __attribute__((aligned(1024))) uint16_t lds_raw[kSplitLdsElems];
   uint16_t (*lds)[4][S_PLANE] = (uint16_t (*)[4][S_PLANE])lds_raw;
-  const int tiles_m = (int)(2 * ldm / S_BM), tiles_n = (int)((ncols + S_BN - 1) / S_BN);
+  constexpr int BN = 64 * NJ;
+  const int tiles_m = (int)(2 * ldm / S_BM), tiles_n = (int)((ncols + BN - 1) / BN);
   int tm, tn;
   if (!tile_of_block(blockIdx.x, tiles_m, tiles_n, tm, tn)) return;
-  split_pp_tile<H, false, PF>(lds, A, B, C, ldm, ncols, kmodes, (int64_t)tm * S_BM, (int64_t)tn * S_BN,
-                              out_scale, nullptr);
+  split_pp_tile<H, false, PF, NJ>(lds, A, B, C, ldm, ncols, kmodes, (int64_t)tm * S_BM,
+                                  (int64_t)tn * BN, out_scale, nullptr, NJ == 4 ? -1 : (int)threadIdx.x);
 }
 
 // Occupation-fused twin of gemm_split_256_pp: tile (tm, tn) covers modes
-// [128 tm, 128 tm + 128) and samples [128 tn, 128 tn + 128); no C is written.
-template <typename H, bool PF>
+// [128 tm, 128 tm + 128) and samples [32 NJ tn, 32 NJ tn + 32 NJ); no C is written.
+template <typename H, bool PF, int NJ>
 __global__ __launch_bounds__(kThreads, 1) void gemm_split_occ(const uint16_t* __restrict__ A,
                                                               const uint16_t* __restrict__ B,
                                                               int64_t ldm, int64_t ncols, int kmodes,
                                                               float out_scale, FusedOut fo) {
   __shared__ __attribute__((aligned(1024))) uint16_t lds_raw[kSplitLdsElems];
   uint16_t (*lds)[4][S_PLANE] = (uint16_t (*)[4][S_PLANE])lds_raw;
-  const int tiles_m = (int)(2 * ldm / S_BM), tiles_n = (int)((ncols + S_BN - 1) / S_BN);
+  const int tiles_m = (int)(2 * ldm / S_BM), tiles_n = (int)((ncols + 64 * NJ - 1) / (64 * NJ));
   int tm, tn;
   if (!tile_of_block(blockIdx.x, tiles_m, tiles_n, tm, tn)) return;
-  split_pp_tile<H, true, PF>(lds, A, B, nullptr, ldm, ncols, kmodes, (int64_t)tm * 128, (int64_t)tn * 128,
-                             out_scale, &fo);
+  split_pp_tile<H, true, PF, NJ>(lds, A, B, nullptr, ldm, ncols, kmodes, (int64_t)tm * 128,
+                                 (int64_t)tn * 32 * NJ, out_scale, &fo,
+                                 NJ == 4 ? -1 : (int)threadIdx.x);
 }
 
 // ---------------------------------------------------------------- one-sided split, 256 x 256
@@ -1769,15 +1772,15 @@ __global__ void bilin_diag(const double* __restrict__ C, int M, int64_t ldm,
 // different bank halves, and the XOR spreads each half over 8 chunk slots).
 // Lane half h supplies k = 16 h + 8 f + s at step s of fragment set f
 // (f = 0, 1; s = 0..7), the same permutation on both operands; set f is
-// chunks 4 h + 2 f and 4 h + 2 f + 1.  Wave w loads half (w & 1) of operand
-// w >> 1.
+// chunks 4 h + 2 f and 4 h + 2 f + 1.
 constexpr int F_BK = 32;
 constexpr int F_PLANE = S_BM * F_BK;  // floats of one LDS operand plane
 
 
 // FUSED: tile (tm, tn) covers modes [128 tm, 128 tm + 128) and samples
 // [128 tn, 128 tn + 128) as in gemm_split_occ, and the epilogue is
-// fused_epilogue.
+// fused_epilogue.  NJ = 2: tiles of 256 x 128 (fused: 128 modes x 64 samples),
+// whose B planes use their first 128 rows (narrow_tiles).
 // Otherwise the launch is persistent: a workgroup takes the tiles of blocks b,
 // b + gridDim.x, ... (gridDim.x is a multiple of 8, so they stay on its XCD), and
 // the slabs of its tiles are one stream: the last two slabs of a tile load the first
@@ -1788,13 +1791,15 @@ constexpr int F_PLANE = S_BM * F_BK;  // floats of one LDS operand plane
 // M = 1000: 5.96 ms, 6.13 ms with a workgroup per tile; 4e4 of M = 512: 630 and 648 us;
 // 1.2e5 of M = 86: 175 and 184 us.  With addresses formed at each load the
 // persistent form gained nothing (6.15 ms).
-template <bool FUSED>
+template <bool FUSED, int NJ>
 __global__ __launch_bounds__(kThreads, 1) void gemm_f32_pp(const float* __restrict__ A,
                                                            const float* __restrict__ B,
                                                            float* __restrict__ C, int64_t ldm,
                                                            int64_t ncols, int kmodes, FusedOut fo) {
   __shared__ __attribute__((aligned(1024))) float lds[2][2][F_PLANE];
-  const int tiles_m = (int)(2 * ldm / S_BM), tiles_n = (int)((ncols + S_BN - 1) / S_BN);
+  constexpr int BN = 64 * NJ;              // columns of a tile
+  constexpr int TN = FUSED ? BN / 2 : BN;  // samples or columns from one tile to the next
+  const int tiles_m = (int)(2 * ldm / S_BM), tiles_n = (int)((ncols + BN - 1) / BN);
   const int blocks = tile_blocks(tiles_m, tiles_n);
   int blk = blockIdx.x, tm, tn;
   // the next block at or after blk with a tile; false past the last
@@ -1807,57 +1812,63 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_f32_pp(const float* __restri
   const int wm = wave >> 1, wn = wave & 1;
   const int lr = lane & 31, lh = lane >> 5;
 
-  const int op = wave >> 1, half = wave & 1;
   const int lrow = lane >> 3;
-  // first column that a tile loads: a ragged last tile takes the last 256 columns and
+  // first column that a tile loads: a ragged last tile takes the last BN columns and
   // stores its own, so the rows below are the same for every tile
-  auto load_col = [&](int64_t n) { return FUSED ? n : max((int64_t)0, min(n, ncols - S_BN)); };
-  // operand rows of tile (tm, tn) that this wave loads; fused tiles' second half of the
-  // rows are the Im rows (A) or the beta columns (B)
-  auto tile_src = [&]() {
-    const int64_t row = op == 0 ? (int64_t)tm * (FUSED ? 128 : S_BM)
-                                : load_col((int64_t)tn * (FUSED ? 128 : S_BN));
-    const int64_t upper = op == 0 ? ldm : ncols / 2;
-    return (op == 0 ? A : B) + (row + (FUSED && half ? upper : 0)) * ldm;
+  auto load_col = [&](int64_t n) { return FUSED ? n : max((int64_t)0, min(n, ncols - BN)); };
+  // The loads of a slab are blocks of 8 rows, 32 of A then 8 NJ of B, shared out in
+  // order to the waves.  Region of block g: A, B (fused: the Re and Im rows of A, the
+  // alpha and beta columns of B); a wave's blocks lie in at most two regions.
+  constexpr int kLoads = 8 + 2 * NJ;
+  auto region = [&](int g) {
+    return FUSED ? (g < 32 ? g / 16 : 2 + (g - 32) / (4 * NJ)) : (g < 32 ? 0 : 1);
   };
-  // lane l writes LDS slot 16 l of each 1 KB block (8 rows): row 8 q + l / 8 of the
-  // wave's half, slot l % 8, which holds global chunk (l % 8) ^ swz8(row).  Rows past
-  // the operand's last are clamped to it
-  const int64_t left = op == 0 ? S_BM : (FUSED ? ncols / 2 - (int64_t)tn * 128 : ncols);
-  uint32_t off[16];  // in bytes
+  const int g0 = wave * kLoads;
+  auto region_src = [&](int rg) {
+    const bool b = rg >= (FUSED ? 2 : 1);
+    const int64_t row = b ? load_col((int64_t)tn * TN) : (int64_t)tm * (FUSED ? 128 : S_BM);
+    const int64_t upper = FUSED && (rg & 1) ? (b ? ncols / 2 : ldm) : 0;
+    return (b ? B : A) + (row + upper) * ldm;
+  };
+  // lane l writes LDS slot 16 l of each 1 KB block: row 8 g + l / 8, slot l % 8, which
+  // holds global chunk (l % 8) ^ swz8(row).  Rows past the operand's last are clamped to it
+  uint32_t off[kLoads];  // in bytes, from the region's first row
+  int n_lo = 0;          // blocks in the first region
 #pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    const int r = (FUSED ? 0 : half * 128) + 8 * q + lrow;
-    const int64_t row = r < left ? r : left - 1;
-    off[q] = (uint32_t)(4 * (row * ldm + (((lane & 7) ^ swz8(r)) << 2)));
+  for (int q = 0; q < kLoads; ++q) {
+    const int g = g0 + q, rg = region(g), r = 8 * (g < 32 ? g : g - 32) + lrow;
+    const int rr = FUSED ? r - (rg & 1) * (g < 32 ? 128 : BN / 2) : r;
+    const int64_t left = g < 32 ? S_BM : (FUSED ? ncols / 2 - (int64_t)tn * TN : ncols);
+    off[q] = (uint32_t)(4 * ((rr < left ? rr : left - 1) * ldm + (((lane & 7) ^ swz8(r)) << 2)));
+    n_lo += rg == region(g0);
   }
-  auto issue = [&](int st, const float* src, int k0) {
-    char* dst = (char*)&lds[st][op][0] + half * (128 * F_BK * 4);
+  auto issue = [&](int st, const float* lo, const float* hi, int k0) {
+    char* dst = (char*)&lds[st][0][0] + g0 * 1024;
 #pragma unroll
-    for (int q = 0; q < 16; ++q)
-      __builtin_amdgcn_global_load_lds((const void*)((const char*)(src + k0) + off[q]),
+    for (int q = 0; q < kLoads; ++q)
+      __builtin_amdgcn_global_load_lds((const void*)((const char*)((q < n_lo ? lo : hi) + k0) + off[q]),
                                        (lds_void*)(dst + q * 1024), 16, 0, 0);
   };
-  int oa[2][2][4], ob[2][2][4];
+  int oa[2][2][4], ob[2][2][NJ];
 #pragma unroll
   for (int f = 0; f < 2; ++f)
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int ra = wm * 128 + i * 32 + lr, rb = wn * 128 + i * 32 + lr;
+        const int ra = wm * 128 + i * 32 + lr, rb = wn * 32 * NJ + i * 32 + lr;
         const int c = 4 * lh + 2 * f + t;
         oa[f][t][i] = ra * F_BK + ((c ^ swz8(ra)) << 2);
-        ob[f][t][i] = rb * F_BK + ((c ^ swz8(rb)) << 2);
+        if (i < NJ) ob[f][t][i] = rb * F_BK + ((c ^ swz8(rb)) << 2);
       }
-  f32x4 a0[2][4], b0[2][4], a1[2][4], b1[2][4];
+  f32x4 a0[2][4], b0[2][NJ], a1[2][4], b1[2][NJ];
   auto read0 = [&](int st) {
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         a0[t][i] = *(const f32x4*)(&lds[st][0][oa[0][t][i]]);
-        b0[t][i] = *(const f32x4*)(&lds[st][1][ob[0][t][i]]);
+        if (i < NJ) b0[t][i] = *(const f32x4*)(&lds[st][1][ob[0][t][i]]);
       }
   };
   auto read1 = [&](int st) {
@@ -1866,33 +1877,33 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_f32_pp(const float* __restri
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         a1[t][i] = *(const f32x4*)(&lds[st][0][oa[1][t][i]]);
-        b1[t][i] = *(const f32x4*)(&lds[st][1][ob[1][t][i]]);
+        if (i < NJ) b1[t][i] = *(const f32x4*)(&lds[st][1][ob[1][t][i]]);
       }
   };
 
   const int KT = kmodes / F_BK;  // even, >= 2
-  const float* src = tile_src();
-  issue(0, src, 0);
-  issue(1, src, F_BK);
+  const float *lo = region_src(region(g0)), *hi = region_src(region(g0 + kLoads - 1));
+  issue(0, lo, hi, 0);
+  issue(1, lo, hi, F_BK);
   wait_vm<0>();
   barrier_no_fence();
   read0(0);
   constexpr int kSgMfma = 0x008, kSgDsRead = 0x100, kSgVmem = 0x020;
-  f32x16 acc[4][4];
+  f32x16 acc[4][NJ];
   int64_t m0, n0;
   bool more;
   do {
-    m0 = (int64_t)tm * (FUSED ? 128 : S_BM), n0 = (int64_t)tn * (FUSED ? 128 : S_BN);
+    m0 = (int64_t)tm * (FUSED ? 128 : S_BM), n0 = (int64_t)tn * TN;
     // the tile after this one, whose first two slabs follow this one's (without one
     // this tile's first slabs are loaded again, in bounds, and not used)
-    const float* nsrc = src;
+    const float *nlo = lo, *nhi = hi;
     blk += gridDim.x;
     more = !FUSED && next_tile();
-    if (more) nsrc = tile_src();
+    if (more) nlo = region_src(region(g0)), nhi = region_src(region(g0 + kLoads - 1));
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+      for (int j = 0; j < NJ; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
     for (int kt = 0; kt < KT; ++kt) {
@@ -1904,15 +1915,17 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_f32_pp(const float* __restri
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
-          for (int j = 0; j < 4; ++j)
+          for (int j = 0; j < NJ; ++j)
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0[s >> 2][i][s & 3], b0[s >> 2][j][s & 3],
                                                              acc[i][j], 0, 0, 0);
+      // per phase: 32 NJ MFMAs, 8 + 2 NJ fragment reads
+      constexpr int kReads = 8 + 2 * NJ;
 #pragma unroll
-      for (int q = 0; q < 16; ++q) {
+      for (int q = 0; q < kReads; ++q) {
         __builtin_amdgcn_sched_group_barrier(kSgMfma, 4, 0);
         __builtin_amdgcn_sched_group_barrier(kSgDsRead, 1, 0);
       }
-      __builtin_amdgcn_sched_group_barrier(kSgMfma, 64, 0);
+      __builtin_amdgcn_sched_group_barrier(kSgMfma, 32 * NJ - 4 * kReads, 0);
       __builtin_amdgcn_sched_barrier(0);
       // own loads of slab kt + 1 landed (a tile's first slabs have before its loop, and
       // the stores of the tile before may still be under way), reads of stage cur done
@@ -1926,35 +1939,36 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_f32_pp(const float* __restri
       // phase B: set 1 (steps 8-15) with the loads of slab kt + 2 and the reads of
       // set 0 of slab kt + 1 threaded in
       const bool own = kt + 2 < KT;
-      issue(cur, own ? src : nsrc, (own ? kt + 2 : kt + 2 - KT) * F_BK);
+      issue(cur, own ? lo : nlo, own ? hi : nhi, (own ? kt + 2 : kt + 2 - KT) * F_BK);
       read0(cur ^ 1);
 #pragma unroll
       for (int s = 0; s < 8; ++s)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
-          for (int j = 0; j < 4; ++j)
+          for (int j = 0; j < NJ; ++j)
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[s >> 2][i][s & 3], b1[s >> 2][j][s & 3],
                                                              acc[i][j], 0, 0, 0);
+      constexpr int kPerLoad = NJ / 2, kPerRead = NJ == 4 ? 4 : 3;
 #pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        __builtin_amdgcn_sched_group_barrier(kSgMfma, 2, 1);
+      for (int q = 0; q < kLoads; ++q) {
+        __builtin_amdgcn_sched_group_barrier(kSgMfma, kPerLoad, 1);
         __builtin_amdgcn_sched_group_barrier(kSgVmem, 1, 1);
       }
 #pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        __builtin_amdgcn_sched_group_barrier(kSgMfma, 4, 1);
+      for (int q = 0; q < kReads; ++q) {
+        __builtin_amdgcn_sched_group_barrier(kSgMfma, kPerRead, 1);
         __builtin_amdgcn_sched_group_barrier(kSgDsRead, 1, 1);
       }
-      __builtin_amdgcn_sched_group_barrier(kSgMfma, 32, 1);
+      __builtin_amdgcn_sched_group_barrier(kSgMfma, 32 * NJ - kLoads * kPerLoad - kReads * kPerRead, 1);
       __builtin_amdgcn_sched_barrier(0);
     }
     wait_vm<0>();  // the next tile's second slab landed
     if constexpr (!FUSED) {
       const int64_t ldc = 2 * ldm;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int64_t col = load_col(n0) + wn * 128 + j * 32 + lr;
+      for (int j = 0; j < NJ; ++j) {
+        const int64_t col = load_col(n0) + wn * 32 * NJ + j * 32 + lr;
         if (col >= n0 && col < ncols) {
 #pragma unroll
           for (int i = 0; i < 4; ++i)
@@ -1966,7 +1980,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_f32_pp(const float* __restri
             }
         }
       }
-      src = nsrc;
+      lo = nlo, hi = nhi;
     }
   } while (more);
   if constexpr (FUSED) {
@@ -1975,7 +1989,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_f32_pp(const float* __restri
     // spilled 41 of them around the epilogue
     float one = 1.0f;
     asm volatile("" : "+s"(one));
-    fused_epilogue(acc, &lds[0][0][0], fo, m0, n0, wm, wn, lane, one);
+    fused_epilogue<NJ>(acc, &lds[0][0][0], fo, m0, n0, wm, wn, lane, one);
   }
 }
 
@@ -2163,13 +2177,39 @@ mp_status pack_launch(int32_t M, const double* T, mp_precision prec, void* packe
   return MP_OK;
 }
 
+// Whether tiles of 256 x 128 end a product (FP32, or split with two 16-bit planes)
+// sooner than 256 x 256: a turn of narrow tiles on all CUs takes 0.55 to 0.63 of one
+// of wide tiles, and the last turn of either may be nearly empty.  Narrow against wide, one
+// turn each (M = 900, 1e3 samples): FP32 125 and 225 us, split FP16 44 and 63 us; three
+// against two (M = 436, 1e4): 196 and 239, 78 and 81 us; two against one (M = 300,
+// 7e3): 86 us wide in FP32, 36 us in split FP16, narrow slower.  Both give the same bits.
+static bool narrow_tiles(int64_t ldm, int64_t ncols) {
+  const int64_t rows = 2 * ldm / S_BM;
+  const int64_t wide = (rows * ((ncols + 255) / 256) + kCus - 1) / kCus;
+  const int64_t narrow = (rows * ((ncols + 127) / 128) + kCus - 1) / kCus;
+  return 13 * narrow < 20 * wide;
+}
+
 // GEMM on an already packed operand (one network).
 template <typename H>
-static void split_gemm(int grid, hipStream_t stream, const void* packed, const void* ab, void* C,
+static void split_gemm(hipStream_t stream, const void* packed, const void* ab, void* C,
                        int64_t ldm, int64_t ncols, int kmodes, float scale) {
-  auto kernel = split_prefetch_for(ldm) ? gemm_split_256_pp<H, true> : gemm_split_256_pp<H, false>;
-  hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), 0, stream, (const uint16_t*)packed,
-                     (const uint16_t*)ab, (float*)C, ldm, ncols, kmodes, scale);
+  const bool pf = split_prefetch_for(ldm), narrow = narrow_tiles(ldm, ncols);
+  auto kernel = narrow ? (pf ? gemm_split_256_pp<H, true, 2> : gemm_split_256_pp<H, false, 2>)
+                       : (pf ? gemm_split_256_pp<H, true, 4> : gemm_split_256_pp<H, false, 4>);
+  hipLaunchKernelGGL(kernel, dim3(grid_tiles(ldm, ncols, S_BM, narrow ? 128 : S_BN)), dim3(kThreads),
+                     0, stream, (const uint16_t*)packed, (const uint16_t*)ab, (float*)C, ldm, ncols,
+                     kmodes, scale);
+}
+template <typename H>
+static void split_occ(hipStream_t stream, const void* packed, const void* ab, int64_t ldm,
+                      int64_t ncols, int kmodes, float scale, const FusedOut& fo) {
+  const bool pf = split_prefetch_for(ldm), narrow = narrow_tiles(ldm, ncols);
+  auto kernel = narrow ? (pf ? gemm_split_occ<H, true, 2> : gemm_split_occ<H, false, 2>)
+                       : (pf ? gemm_split_occ<H, true, 4> : gemm_split_occ<H, false, 4>);
+  hipLaunchKernelGGL(kernel, dim3(grid_tiles(ldm, ncols, S_BM, narrow ? 128 : S_BN)), dim3(kThreads),
+                     0, stream, (const uint16_t*)packed, (const uint16_t*)ab, ldm, ncols, kmodes,
+                     scale, fo);
 }
 
 bool split_prefetch(int64_t ldm) { return split_prefetch_for(ldm); }
@@ -2177,22 +2217,24 @@ bool split_prefetch(int64_t ldm) { return split_prefetch_for(ldm); }
 mp_status gemm_packed_launch(int32_t M, int64_t E, const void* packed, mp_precision prec,
                              const void* ab, void* C, hipStream_t stream) {
   const int64_t ldm = ld_modes(M), ncols = 2 * E;
+  const bool narrow = narrow_tiles(ldm, ncols);
   switch (prec) {
     case MP_FP64:
       hipLaunchKernelGGL(gemm_f64_pp, dim3(grid_tiles(ldm, ncols, D_BM, D_BN)), dim3(kThreads), 0,
                          stream, (const double*)packed, (const double*)ab, (double*)C, ldm, ncols, k_modes(M, D_BK));
       break;
     case MP_FP32:
-      hipLaunchKernelGGL(gemm_f32_pp<false>, dim3(min(grid_tiles(ldm, ncols, S_BM, S_BN), kCus)),
+      hipLaunchKernelGGL((narrow ? gemm_f32_pp<false, 2> : gemm_f32_pp<false, 4>),
+                         dim3(min(grid_tiles(ldm, ncols, S_BM, narrow ? 128 : S_BN), kCus)),
                          dim3(kThreads), 0, stream, (const float*)packed, (const float*)ab,
                          (float*)C, ldm, ncols, k_modes(M), FusedOut{});
       break;
     case MP_SPLIT_BF16:
-      split_gemm<__bf16>(grid_tiles(ldm, ncols, S_BM, S_BN), stream, packed, ab, C, ldm, ncols, k_modes(M),
+      split_gemm<__bf16>(stream, packed, ab, C, ldm, ncols, k_modes(M),
                          1.0f);
       break;
     case MP_SPLIT_FP16:
-      split_gemm<_Float16>(grid_tiles(ldm, ncols, S_BM, S_BN), stream, packed, ab, C, ldm, ncols, k_modes(M),
+      split_gemm<_Float16>(stream, packed, ab, C, ldm, ncols, k_modes(M),
                            ldexpf(1.0f, -fp16_scale_exp(M)));
       break;
     case MP_SPLIT1_FP16: {
@@ -2262,24 +2304,20 @@ mp_status gemm_fused_launch(int32_t M, int64_t E, const void* packed, mp_precisi
                             const void* ab, const FusedOut& fo, hipStream_t stream) {
   const int64_t ldm = ld_modes(M), ncols = 2 * E;
   const int grid = grid_tiles(ldm, ncols, S_BM, S_BN);
+  const bool narrow = narrow_tiles(ldm, ncols);
   switch (prec) {
     case MP_FP32:
-      hipLaunchKernelGGL(gemm_f32_pp<true>, dim3(grid), dim3(kThreads), 0, stream,
+      hipLaunchKernelGGL((narrow ? gemm_f32_pp<true, 2> : gemm_f32_pp<true, 4>),
+                         dim3(grid_tiles(ldm, ncols, S_BM, narrow ? 128 : S_BN)), dim3(kThreads), 0, stream,
                          (const float*)packed, (const float*)ab, (float*)nullptr, ldm, ncols, k_modes(M), fo);
       break;
-    case MP_SPLIT_BF16: {
-      auto kernel = split_prefetch_for(ldm) ? gemm_split_occ<__bf16, true> : gemm_split_occ<__bf16, false>;
-      hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), 0, stream, (const uint16_t*)packed,
-                         (const uint16_t*)ab, ldm, ncols, k_modes(M), 1.0f, fo);
+    case MP_SPLIT_BF16:
+      split_occ<__bf16>(stream, packed, ab, ldm, ncols, k_modes(M), 1.0f, fo);
       break;
-    }
-    case MP_SPLIT_FP16: {
-      auto kernel =
-          split_prefetch_for(ldm) ? gemm_split_occ<_Float16, true> : gemm_split_occ<_Float16, false>;
-      hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), 0, stream, (const uint16_t*)packed,
-                         (const uint16_t*)ab, ldm, ncols, k_modes(M), ldexpf(1.0f, -fp16_scale_exp(M)), fo);
+    case MP_SPLIT_FP16:
+      split_occ<_Float16>(stream, packed, ab, ldm, ncols, k_modes(M), ldexpf(1.0f, -fp16_scale_exp(M)),
+                          fo);
       break;
-    }
     case MP_SPLIT1_FP16: {
       auto kernel = split_prefetch_for(ldm) ? gemm_split1_occ<true> : gemm_split1_occ<false>;
       hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), 0, stream, (const uint16_t*)packed,

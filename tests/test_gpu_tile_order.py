@@ -54,3 +54,31 @@ def test_tiles_past_the_first_turn(M, E):
     rows = np.linalg.norm(T, axis=1)
     for x, got, want in ((a, ga, a @ T.T), (b, gb, b @ T.conj().T)):
         assert np.all(np.abs(got - want) <= u * np.linalg.norm(x, axis=1)[:, None] * rows)
+
+
+@pytest.mark.parametrize("prec", ["split_bf16", "split_fp16"])
+@pytest.mark.parametrize("M,E", [(3, 1), (100, 65), (300, 1000), (520, 3210)])
+def test_fused_and_stored_products_agree(prec, M, E):
+    """Occupations from the stored product and from the fused one, in products of narrow tiles
+    (one turn, or three against two).  The stored product's FP64 sums differ from the fused
+    FP32 sums by at most 64 + 8 roundings of sum |alpha'_j beta'_j| per 128-mode block half,
+    and so do n_q and, twice over, every term."""
+    import torch
+
+    import paper_2503_12749_amd as mp
+    rng = np.random.default_rng(M + E)
+    T = (rng.standard_normal((M, M)) + 1j * rng.standard_normal((M, M))) / np.sqrt(2 * M) * 0.7
+    accs = []
+    for fused in (False, True):
+        p = mp.CountsPipeline(T, np.linspace(0.2, 0.5, M), prec=prec, seed=3, d=1, mode="joint",
+                              bin_of_mode=np.zeros(M, np.int32), windows=[(0, 24)], n_sub=1,
+                              samples_per_sub=E, chunk=E, fused=fused)
+        p.run_chunk(0, E)
+        accs.append(p.acc.cpu().numpy().view(complex))
+        if not fused:
+            a, b = p.propagated(E)
+            dn = 72 * 2.0 ** -24 * np.abs(a * b).sum(1).max()
+    # terms of at most e^(2 |n|) each lose 2 dn and FP32 roundings of exponents up to 46
+    n = np.abs((a * b).sum(1))
+    size = np.exp(2 * np.minimum(n, 20)).sum()
+    assert np.all(np.abs(accs[0] - accs[1]) <= (4 * dn + 2 * 62 * 2.0 ** -24) * size)
