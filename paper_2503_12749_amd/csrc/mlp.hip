@@ -65,21 +65,28 @@ struct MlpNet {
 
 // Prediction (no gradients): one layer, A = SiLU(X W + b) (the last layer linear),
 // 64 x 64 tiles of four waves with v_mfma_f32_32x32x16_bf16 on the three BF16 terms
-// of X, staging 32-deep K chunks in LDS: X as three BF16 planes [row][k] and W
-// transposed as [col][k] (80-byte rows: the 16-byte fragment reads of 16
-// consecutive rows hit distinct banks).  Lane l holds X[l % 32][8 (l / 32) + e],
+// of X, staging K chunks in LDS: X as three BF16 planes [row][k] and W
+// transposed as [col][k] (rows padded by 16 bytes: the 16-byte fragment reads of
+// 16 consecutive rows hit distinct banks).  Lane l holds X[l % 32][8 (l / 32) + e],
 // W[8 (l / 32) + e][l % 32] (e = 0..7) of a 16-deep step; output register r is row
 // 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32 of the wave's block.  mlp_rows
 // below would take less time here too, but sums in another order, and predictions
 // are handed out in double precision: they keep their values to the last bit.
-constexpr int MLP_T = 64, MLP_KC = 32, MLP_KP = MLP_KC + 8, MLP_THREADS = 256;
+constexpr int MLP_T = 64, MLP_THREADS = 256;
 
+// KC: depth of a staged K chunk (32 for layers of up to 32 inputs, else 128).  Bound by the
+// latency of a chunk: its loads are all issued before the first is used, and the deeper
+// chunk takes a quarter of the turns.  512 rows, layers of 5, 208, 55, 307, 51 and 8:
+// 11.2 us a layer of more than 32 inputs (20.4 us with 32-deep chunks loaded as used).
+template <int KC>
 __global__ __launch_bounds__(MLP_THREADS) void mlp_layer(const float* __restrict__ Aop,
                                                      const uint16_t* __restrict__ W16, int R,
                                                      int K, int N, const float* __restrict__ bias,
                                                      float* __restrict__ Act, int silu) {
-  __shared__ __attribute__((aligned(16))) uint16_t sA[3][MLP_T][MLP_KP];
-  __shared__ __attribute__((aligned(16))) uint16_t sB[MLP_T][MLP_KP];
+  constexpr int KP = KC + 8, kPer = MLP_T * KC / MLP_THREADS;  // values of X and of W per thread
+  extern __shared__ __attribute__((aligned(16))) uint16_t mlp_layer_lds[];
+  uint16_t(*sA)[MLP_T][KP] = (uint16_t(*)[MLP_T][KP])mlp_layer_lds;
+  uint16_t(*sB)[KP] = (uint16_t(*)[KP])(mlp_layer_lds + 3 * MLP_T * KP);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int r0 = blockIdx.x * MLP_T, n0 = blockIdx.y * MLP_T;
   const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32;
@@ -87,24 +94,41 @@ __global__ __launch_bounds__(MLP_THREADS) void mlp_layer(const float* __restrict
   f32x16 acc;
 #pragma unroll
   for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
-  for (int k0 = 0; k0 < K; k0 += MLP_KC) {
-    for (int e = threadIdx.x; e < MLP_T * MLP_KC; e += MLP_THREADS) {
-      const int r = e / MLP_KC, k = e % MLP_KC;
-      const float x = (r0 + r < R && k0 + k < K) ? Aop[(int64_t)(r0 + r) * K + k0 + k] : 0.0f;
-      const uint16_t h = to_bf16(x);
-      const float x1 = x - bf16f(h);
+  for (int k0 = 0; k0 < K; k0 += KC) {
+    float x[kPer];
+    uint16_t w[kPer];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      const int e = threadIdx.x + i * MLP_THREADS;
+      const int r = min(r0 + e / KC, R - 1), k = min(k0 + e % KC, K - 1);
+      x[i] = Aop[(int64_t)r * K + k];
+    }
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      const int e = threadIdx.x + i * MLP_THREADS;  // coalesced along n
+      const int k = min(k0 + e / MLP_T, K - 1), n = min(n0 + e % MLP_T, N - 1);
+      w[i] = W16[(int64_t)k * N + n];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      const int e = threadIdx.x + i * MLP_THREADS, r = e / KC, k = e % KC;
+      const float v = (r0 + r < R && k0 + k < K) ? x[i] : 0.0f;
+      const uint16_t h = to_bf16(v);
+      const float x1 = v - bf16f(h);
       const uint16_t m = to_bf16(x1);
       sA[0][r][k] = h;
       sA[1][r][k] = m;
       sA[2][r][k] = to_bf16(x1 - bf16f(m));
     }
-    for (int e = threadIdx.x; e < MLP_T * MLP_KC; e += MLP_THREADS) {
-      const int k = e / MLP_T, n = e % MLP_T;  // coalesced along n
-      sB[n][k] = (k0 + k < K && n0 + n < N) ? W16[(int64_t)(k0 + k) * N + n0 + n] : (uint16_t)0;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      const int e = threadIdx.x + i * MLP_THREADS, k = e / MLP_T, n = e % MLP_T;
+      sB[n][k] = (k0 + k < K && n0 + n < N) ? w[i] : (uint16_t)0;
     }
     __syncthreads();
-#pragma unroll
-    for (int ks = 0; ks < MLP_KC; ks += 16) {
+    const int depth = min(KC, (K - k0 + 15) & ~15);  // past it are zeros
+    for (int ks = 0; ks < depth; ks += 16) {
       const int kk = ks + 8 * lh;
       const bf16x8 b = *(const bf16x8*)&sB[wc + lr][kk];
       // small terms first
@@ -114,7 +138,6 @@ __global__ __launch_bounds__(MLP_THREADS) void mlp_layer(const float* __restrict
         acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
       }
     }
-    __syncthreads();
   }
   const int col = n0 + wc + lr;
   if (col >= N) return;
@@ -633,9 +656,14 @@ mp_status mlp_forward(const mp_mlp_shape* s, const uint16_t* w16, const float* p
     // one layer reads X while it writes: through the workspace, as Y may be X
     float* act = last && l > 0 ? Y : cur;
     cur += (int64_t)batch * O;
-    hipLaunchKernelGGL(mlp_layer,
+    const int KC = I <= 32 ? 32 : 128;
+    auto kernel = KC == 32 ? mlp_layer<32> : mlp_layer<128>;
+    const size_t lds = (size_t)4 * MLP_T * (KC + 8) * 2;
+    const mp_status r = mlp_lds((const void*)kernel, lds);
+    if (r != MP_OK) return r;
+    hipLaunchKernelGGL(kernel,
                        dim3((unsigned)((batch + MLP_T - 1) / MLP_T), (unsigned)((O + MLP_T - 1) / MLP_T)),
-                       dim3(MLP_THREADS), 0, st, in, w16 + off, (int)batch, I, O,
+                       dim3(MLP_THREADS), lds, st, in, w16 + off, (int)batch, I, O,
                        params + off + (int64_t)I * O, act, last ? 0 : 1);
     in = act;
   }
