@@ -90,13 +90,18 @@ __device__ inline void run_sum(const CT* __restrict__ ca, const CT* __restrict__
 }
 
 // Whether a row of 16 lanes per sample reads the runs sooner than a wave: up to an
-// average run of 512 bytes (128 modes in FP32, 64 in FP64).  Occupations by rows
-// against waves, FP32, 1.2e5 samples or 4e7 amplitudes: 39 and 138 us at six runs of
-// 14 modes, 79 and 101 us at two of 100, 132 and 134 us at eight of 125, 132 and
+// average run of `bytes`.  The observables' occupations take 512 (128 modes in FP32):
+// by rows against waves, FP32, 1.2e5 samples or 4e7 amplitudes, 39 and 138 us at six
+// runs of 14 modes, 79 and 101 us at two of 100, 132 and 134 us at eight of 125, 132 and
 // 126 us at four of 150; FP64: 86 and 145 us at six of 14, 75 and 75 us at two of
-// 50, 102 and 101 us at two of 65, 136 and 135 us at two of 100.
-inline bool short_runs(int64_t M, int64_t n_runs, size_t elem) {
-  return M * (int64_t)elem <= 512 * n_runs;
+// 50, 136 and 135 us at two of 100.  counts_fused, whose workgroups have fewer samples
+// to overlap, takes 2048: with the counting, 1e4 samples, 40 and 50 us at two of 100, 46
+// and 52 us at two of 218, 34 and 41 us at one of 436, 49 and 47 us at one of 1000;
+// 1e5 samples: 430 and 453 us at four of 250, 353 and 349 us at one of 1000; FP64,
+// 1e4: 31 and 34 us at one of 16, 52 and 61 us at two of 50, 49 and 49 us at one of 400.
+constexpr int kRowBytesOcc = 512, kRowBytesCounts = 2048;
+inline bool short_runs(int64_t M, int64_t n_runs, size_t elem, int bytes) {
+  return M * (int64_t)elem <= bytes * n_runs;
 }
 
 // One sample's occupation sum over one bin run from the occupation-fused

@@ -91,22 +91,22 @@ __device__ inline void block_samples(const CountsParams& p, int b, int64_t& s, i
 // in LDS for every bin b < d, behind a barrier; red is LDS scratch.
 typedef __attribute__((ext_vector_type(2))) double d2;
 
-template <typename CT>
+template <typename CT, int G>
 struct FromC {
   const CT* C;
-  // wave per sample, lanes over modes
+  // G lanes per sample over its modes: a wave, or a row of 16 (four samples at a time)
   __device__ inline void bin_sums(const CountsParams& p, int64_t k0, int nsmp,
                                   d2 (*nb)[kMaxDist], d2*) const {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int gl = threadIdx.x % G;
     const int64_t ldc = 2 * p.ldm;
-    for (int i = wave; i < nsmp; i += kCountThreads / 64) {
+    for (int i = threadIdx.x / G; i < nsmp; i += kCountThreads / G) {
       const int64_t k = k0 + i;
-      if (lane == 0)
+      if (gl == 0)
         for (int b = 0; b < p.d; ++b) nb[i][b] = d2{0.0, 0.0};
       for (int q = 0; q < p.n_runs; ++q) {
         double re, im;
-        run_sum<CT>(C + k * ldc, C + (p.E + k) * ldc, p.ldm, p.run_lo[q], p.run_hi[q], lane, re, im);
-        if (lane == 0) nb[i][p.run_bin[q]] += d2{re, im};
+        run_sum<CT, G>(C + k * ldc, C + (p.E + k) * ldc, p.ldm, p.run_lo[q], p.run_hi[q], gl, re, im);
+        if (gl == 0) nb[i][p.run_bin[q]] += d2{re, im};
       }
     }
     __syncthreads();
@@ -1037,11 +1037,16 @@ mp_status binned_counts_launch(int32_t M, int64_t E, const void* C, const double
   const size_t need = (size_t)blocks * (size_t)p.entries * 16;
   MP_CHECK_ARG(ws && ws_bytes >= need, MP_ERR_WORKSPACE,
                "mp_binned_counts: workspace of %zu bytes needed, %zu given", need, ws_bytes);
+  auto go = [&](auto src, auto f64) {
+    return counts_go<decltype(src), decltype(f64)::value>("mp_binned_counts", p, src, n, (double*)ws,
+                                                          acc, stream);
+  };
+  const bool rows = short_runs(M, p.n_runs, elem_bytes_c(prec), kRowBytesCounts);
   if (prec == MP_FP64)
-    return counts_go<FromC<double>, true>("mp_binned_counts", p, FromC<double>{(const double*)C}, n,
-                                          (double*)ws, acc, stream);
-  return counts_go<FromC<float>, false>("mp_binned_counts", p, FromC<float>{(const float*)C}, n,
-                                        (double*)ws, acc, stream);
+    return rows ? go(FromC<double, 16>{(const double*)C}, std::true_type{})
+                : go(FromC<double, 64>{(const double*)C}, std::true_type{});
+  return rows ? go(FromC<float, 16>{(const float*)C}, std::false_type{})
+              : go(FromC<float, 64>{(const float*)C}, std::false_type{});
 }
 
 mp_status gemm_fused_launch(int32_t M, int64_t E, const void* packed, mp_precision prec,
@@ -1579,7 +1584,7 @@ mp_status occupations_launch(int32_t M, int64_t E, const void* C, mp_precision p
   }
   p.n_dist = d + (mode == MP_MARGINALS_AND_TOTAL ? 1 : 0);
   for (int q = 0; q < p.n_dist; ++q) p.dist_src[q] = q < d ? q : -1;
-  const bool row = short_runs(M, p.n_runs, elem_bytes_c(prec));
+  const bool row = short_runs(M, p.n_runs, elem_bytes_c(prec), kRowBytesOcc);
   const int64_t per = 4 * kOccPerWave * (row ? 4 : 1);
   const dim3 grid((unsigned)((E + per - 1) / per));
   auto go = [&](auto kernel, auto* c) {

@@ -60,3 +60,38 @@ def test_occupations_of_runs(prec, mode, M, E, runs):
         for comp, x, y in ((0, a * c, b * e), (1, b * c, -a * e)):
             tol = u * (np.abs(x) + np.abs(y))[:, m].sum(1)
             assert np.all(np.abs(got[:, q, comp] - (x + y)[:, m].sum(1)) <= tol), (q, comp)
+
+
+@pytest.mark.parametrize("prec,M", [("fp32", 30), ("fp32", 1023), ("fp32", 1027), ("fp64", 511), ("fp64", 515)])
+@pytest.mark.parametrize("E", [1, 5, 67])
+def test_counts_on_both_sides_of_the_row_line(prec, M, E):
+    """Two runs that start off the 16-byte boundaries, averages around 2048 bytes of each matrix
+    row.  A bin sum's rounding is below the FP32 rounding of exponents and phases by far; the
+    bound is the counting test's, with the bin sums' own (M u) in FP64."""
+    import torch
+
+    import paper_2503_12749_amd as mp
+    from test_gpu_counts_tiles import _sums
+    rng = np.random.default_rng(M + E)
+    dt = np.float64 if prec == "fp64" else np.float32
+    h = M // 2
+    bins = _bins(M, [(1, h, 0), (h, M, 1)])
+    ldm = mp.mp_ld_modes(M)
+    C = np.full((2 * E, 2, ldm), np.nan, dtype=dt)
+    C[:, :, :M] = (rng.standard_normal((2 * E, 2, M)) / np.sqrt(M)).astype(dt)
+    C[:E, 0, :M] += dt(3 / np.sqrt(M))
+    C[E:, 0, :M] += dt(3 / np.sqrt(M))
+    C[:, :, 0] = np.nan
+    X = C[:, :, :M].astype(np.float64)
+    nj = (X[:E, 0] + 1j * X[:E, 1]) * (X[E:, 0] - 1j * X[E:, 1])
+    occ = [nj[:, bins == q].sum(1) for q in range(2)]
+    n = rng.uniform(2, 6, E)
+    K = (40, 64)
+    acc = torch.zeros(sum(K) * 2, dtype=torch.float64, device="cuda")
+    ws = torch.empty(mp.mp_binned_workspace(2, "marginals", K, E, 1, E, 0), dtype=torch.uint8, device="cuda")
+    mp.mp_binned_counts(M, E, torch.from_numpy(C.reshape(-1)).cuda(), torch.from_numpy(n).cuda(), prec,
+                        "matrix_p", 2, bins, "marginals", (0, 0), K, 1, E, 0, acc, ws)
+    ref, mag = _sums(occ, n, [(0, k) for k in K], 0, E, 1, False)
+    u, arg = (2.0 ** -24, 46.0) if prec == "fp32" else (2.0 ** -53, 46 + 32 * 20 + M)
+    got = acc.cpu().numpy().view(complex)
+    assert np.all(np.abs(got - ref[0]) <= 2 * (arg + 16) * u * mag[0] + E * np.exp(-46.0))
