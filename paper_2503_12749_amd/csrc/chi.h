@@ -15,8 +15,8 @@ namespace mp {
 // (an average of those means) by less than 1e-20 absolute.
 constexpr double kLogEps = -46.0;
 
-// Samples per wave of the per-sample occupation kernels (one wave per sample
-// at a time, lanes over modes).  About twelve waves run per CU: 1e5 samples are 8.1
+// Samples per wave, or row of 16 lanes, of the per-sample occupation kernels (one at a
+// time, lanes over modes).  About twelve waves run per CU: 1e5 samples are 8.1
 // turns of them (16 samples per wave left 2.03, the third nearly empty).
 constexpr int kOccPerWave = 4;
 
@@ -107,17 +107,18 @@ inline bool short_runs(int64_t M, int64_t n_runs, size_t elem, int bytes) {
 // One sample's occupation sum over one bin run from the occupation-fused
 // GEMM's partials: the run's slots [slot0, slot0 + nblk) (one per 128-mode
 // block it touches), four floats per (slot, sample) at part[(slot E + k) 4]:
-// (re, im) from the Re-row half and from the Im-row half.  Wave-reduced.
+// (re, im) from the Re-row half and from the Im-row half.  Summed over G lanes.
+template <int G>
 __device__ inline void run_sum_partials(const float* __restrict__ part, int64_t E, int slot0,
-                                        int nblk, int64_t k, int lane, double& re, double& im) {
+                                        int nblk, int64_t k, int gl, double& re, double& im) {
   double sr = 0.0, si = 0.0;
-  for (int t = lane; t < nblk; t += 64) {
+  for (int t = gl; t < nblk; t += G) {
     const float4 v = *(const float4*)(part + ((int64_t)(slot0 + t) * E + k) * 4);
     sr += (double)v.x + (double)v.z;
     si += (double)v.y + (double)v.w;
   }
-  re = wave_sum(sr);
-  im = wave_sum(si);
+  re = group_sum<G>(sr);
+  im = group_sum<G>(si);
 }
 
 // Slots of a run [lo, hi) in the fused partials: the 128-mode blocks it touches.

@@ -385,17 +385,17 @@ struct Joint2Params {
   int64_t s_first, s_last;
 };
 
-// Per-sample record (one wave per sample, lane 0 writes): n1, n2 (complex),
+// Per-sample record (G lanes per sample, the first writes): n1, n2 (complex),
 // c1, c2 (c2 = -inf for +P; both NaN for a sample that is not finite).
 // record_bands then sets the chunk's bands
 // band[0..3] = u1, u2, v1, v2 half-widths (atomic max, -1 = empty).
 // PART: the bin sums come from the occupation-fused GEMM's partials (slots in
 // run order) instead of the propagated amplitudes C.
-template <typename CT, bool PART>
+template <typename CT, bool PART, int G>
 __device__ inline void joint2_sample(const Joint2Params& p, const CT* __restrict__ C,
                                      const float* __restrict__ part,
                                      const double* __restrict__ nglob, double* __restrict__ rec,
-                                     int64_t k, int lane) {
+                                     int64_t k, int gl) {
   const int64_t ldc = 2 * p.ldm;
   const CT* ca = PART ? nullptr : C + k * ldc;
   const CT* cb = PART ? nullptr : C + (p.E + k) * ldc;
@@ -405,10 +405,10 @@ __device__ inline void joint2_sample(const Joint2Params& p, const CT* __restrict
     double re, im;
     if constexpr (PART) {
       const int nblk = run_blocks(p.run_lo[q], p.run_hi[q]);
-      run_sum_partials(part, p.E, slot0, nblk, k, lane, re, im);
+      run_sum_partials<G>(part, p.E, slot0, nblk, k, gl, re, im);
       slot0 += nblk;
     } else {
-      run_sum<CT>(ca, cb, p.ldm, p.run_lo[q], p.run_hi[q], lane, re, im);
+      run_sum<CT, G>(ca, cb, p.ldm, p.run_lo[q], p.run_hi[q], gl, re, im);
     }
     const bool first = p.run_bin[q] == 0;
     R1 += first ? re : 0.0;
@@ -416,7 +416,7 @@ __device__ inline void joint2_sample(const Joint2Params& p, const CT* __restrict
     R2 += first ? 0.0 : re;
     I2 += first ? 0.0 : im;
   }
-  if (lane != 0) return;
+  if (gl != 0) return;
   const double n = nglob[k];
   const bool sums_finite = isfinite(R1) && isfinite(I1) && isfinite(R2) && isfinite(I2);
   double c1 = 0.0, c2 = -INFINITY;
@@ -433,17 +433,17 @@ __device__ inline void joint2_sample(const Joint2Params& p, const CT* __restrict
   r[5] = c2;
 }
 
-template <typename CT, bool PART>
+template <typename CT, bool PART, int G>
 __global__ __launch_bounds__(256) void joint2_occupations(Joint2Params p, const CT* __restrict__ C,
                                                           const float* __restrict__ part,
                                                           const double* __restrict__ nglob,
                                                           double* __restrict__ rec) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int64_t base = (int64_t)blockIdx.x * (4 * kOccPerWave) + wave;
+  constexpr int S = 256 / G;  // samples of a workgroup at a time
+  const int64_t base = (int64_t)blockIdx.x * (S * kOccPerWave) + threadIdx.x / G;
   for (int j = 0; j < kOccPerWave; ++j) {
-    const int64_t k = base + 4 * j;
+    const int64_t k = base + S * j;
     if (k >= p.E) return;
-    joint2_sample<CT, PART>(p, C, part, nglob, rec, k, lane);
+    joint2_sample<CT, PART, G>(p, C, part, nglob, rec, k, threadIdx.x % G);
   }
 }
 
@@ -699,16 +699,22 @@ mp_status joint2_launch(int32_t M, int64_t E, const void* C, const double* n, mp
   int* band = (int*)ws;
   double* rec = (double*)((char*)ws + 256);
   hipLaunchKernelGGL(joint2_band_init, dim3(1), dim3(64), 0, stream, band);
-  const unsigned blocks = (unsigned)((E + 4 * kOccPerWave - 1) / (4 * kOccPerWave));
+  // rows of 16 lanes also for the partials, of which a run has few (1.15e5 samples of
+  // M = 223: 22 us, 72 us by waves)
+  const bool rows = part || short_runs(M, p.n_runs, elem_bytes_c(prec), kRowBytesOcc);
+  const int64_t per = kOccPerWave * (rows ? 16 : 4);
+  auto occ = [&](auto kernel, auto* c) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((E + per - 1) / per)), dim3(256), 0, stream, p, c, part,
+                       n, rec);
+  };
   if (part)
-    hipLaunchKernelGGL((joint2_occupations<float, true>), dim3(blocks), dim3(256), 0, stream, p,
-                       (const float*)nullptr, part, n, rec);
+    occ(joint2_occupations<float, true, 16>, (const float*)nullptr);
   else if (prec == MP_FP64)
-    hipLaunchKernelGGL((joint2_occupations<double, false>), dim3(blocks), dim3(256), 0, stream, p,
-                       (const double*)C, (const float*)nullptr, n, rec);
+    occ(rows ? joint2_occupations<double, false, 16> : joint2_occupations<double, false, 64>,
+        (const double*)C);
   else
-    hipLaunchKernelGGL((joint2_occupations<float, false>), dim3(blocks), dim3(256), 0, stream, p,
-                       (const float*)C, (const float*)nullptr, n, rec);
+    occ(rows ? joint2_occupations<float, false, 16> : joint2_occupations<float, false, 64>,
+        (const float*)C);
   MP_HIP_LAUNCH_CHECK("mp_binned_counts joint occupations launch");
   const mp_status sb = record_bands_launch(rec, E, 2, K, 2, band, stream);
   if (sb != MP_OK) return sb;

@@ -61,17 +61,17 @@ __global__ void band_init(int* band) {
   if (threadIdx.x < 2 * kJD) band[threadIdx.x] = -1;
 }
 
-// Per sample (one wave, lane 0 writes): the record (Re n_b, Im n_b for b < d,
+// Per sample (a wave, or a row of 16 lanes; the first lane writes): the record (Re n_b, Im n_b for b < d,
 // c1, c2; c2 = -inf for +P, both NaN for a sample that is not finite).
 // record_bands then sets the box half-widths
 // band[term * 4 + b] (atomic max; -1 = term absent).
 // PART: the bin sums come from the occupation-fused GEMM's partials (slots in
 // run order) instead of the propagated amplitudes C.
-template <typename CT, bool PART>
+template <typename CT, bool PART, int G>
 __device__ inline void jointd_sample(const JointDParams& p, const CT* __restrict__ C,
                                      const float* __restrict__ part,
                                      const double* __restrict__ nglob, double* __restrict__ rec,
-                                     int64_t k, int lane) {
+                                     int64_t k, int gl) {
   const int64_t ldc = 2 * p.ldm;
   const CT* ca = PART ? nullptr : C + k * ldc;
   const CT* cb = PART ? nullptr : C + (p.E + k) * ldc;
@@ -81,10 +81,10 @@ __device__ inline void jointd_sample(const JointDParams& p, const CT* __restrict
     double re, im;
     if constexpr (PART) {
       const int nblk = run_blocks(p.run_lo[q], p.run_hi[q]);
-      run_sum_partials(part, p.E, slot0, nblk, k, lane, re, im);
+      run_sum_partials<G>(part, p.E, slot0, nblk, k, gl, re, im);
       slot0 += nblk;
     } else {
-      run_sum<CT>(ca, cb, p.ldm, p.run_lo[q], p.run_hi[q], lane, re, im);
+      run_sum<CT, G>(ca, cb, p.ldm, p.run_lo[q], p.run_hi[q], gl, re, im);
     }
 #pragma unroll
     for (int b = 0; b < kJD; ++b)
@@ -93,7 +93,7 @@ __device__ inline void jointd_sample(const JointDParams& p, const CT* __restrict
         ni[b] += im;
       }
   }
-  if (lane != 0) return;
+  if (gl != 0) return;
   const double n = nglob[k];
   double* r = rec + k * p.rec;
   bool sums_finite = true;
@@ -113,17 +113,17 @@ __device__ inline void jointd_sample(const JointDParams& p, const CT* __restrict
   r[2 * p.d + 1] = c2;
 }
 
-template <typename CT, bool PART>
+template <typename CT, bool PART, int G>
 __global__ __launch_bounds__(256) void jointd_occupations(JointDParams p, const CT* __restrict__ C,
                                                           const float* __restrict__ part,
                                                           const double* __restrict__ nglob,
                                                           double* __restrict__ rec) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int64_t base = (int64_t)blockIdx.x * (4 * kOccPerWave) + wave;
+  constexpr int S = 256 / G;  // samples of a workgroup at a time
+  const int64_t base = (int64_t)blockIdx.x * (S * kOccPerWave) + threadIdx.x / G;
   for (int j = 0; j < kOccPerWave; ++j) {
-    const int64_t k = base + 4 * j;
+    const int64_t k = base + S * j;
     if (k >= p.E) return;
-    jointd_sample<CT, PART>(p, C, part, nglob, rec, k, lane);
+    jointd_sample<CT, PART, G>(p, C, part, nglob, rec, k, threadIdx.x % G);
   }
 }
 
@@ -890,17 +890,26 @@ mp_status jointd_launch(int32_t M, int64_t E, const void* C, const double* n, mp
   double* rec = (double*)((char*)ws + 256);
   void* tables = (char*)ws + 256 + round_up(E * p.rec * 8, 256);
   hipLaunchKernelGGL(band_init, dim3(1), dim3(64), 0, stream, band);
-  const unsigned blocks = (unsigned)((E + 4 * kOccPerWave - 1) / (4 * kOccPerWave));
+  // rows of 16 lanes also for the partials, of which a run has few (amplitudes, 1e5 samples
+  // of three bins of 100 modes: 144 us, 186 us by waves)
+  const bool rows = part || short_runs(M, p.n_runs, elem_bytes_c(prec), kRowBytesOcc);
+  const int64_t per = kOccPerWave * (rows ? 16 : 4);
+  auto occ = [&](auto kernel, auto* c) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((E + per - 1) / per)), dim3(256), 0, stream, p, c, part,
+                       n, rec);
+  };
+  if (part)
+    occ(jointd_occupations<float, true, 16>, (const float*)nullptr);
+  else if (prec == MP_FP64)
+    occ(rows ? jointd_occupations<double, false, 16> : jointd_occupations<double, false, 64>,
+        (const double*)C);
+  else
+    occ(rows ? jointd_occupations<float, false, 16> : jointd_occupations<float, false, 64>,
+        (const float*)C);
   int kp_max = 0;
   for (int b = 0; b < d; ++b) kp_max = p.Kp[b] > kp_max ? p.Kp[b] : kp_max;
   const dim3 fgrid((unsigned)((E * kp_max + 255) / 256), (unsigned)(2 * d));
   if (prec == MP_FP64) {
-    if (part)
-      hipLaunchKernelGGL((jointd_occupations<float, true>), dim3(blocks), dim3(256), 0, stream, p,
-                         (const float*)nullptr, part, n, rec);
-    else
-      hipLaunchKernelGGL((jointd_occupations<double, false>), dim3(blocks), dim3(256), 0, stream,
-                         p, (const double*)C, (const float*)nullptr, n, rec);
     const mp_status sb = record_bands_launch(rec, E, d, K, kJD, band, stream);
     if (sb != MP_OK) return sb;
     hipLaunchKernelGGL(jointd_factors<double>, fgrid, dim3(256), 0, stream, p, rec, band,
@@ -909,19 +918,13 @@ mp_status jointd_launch(int32_t M, int64_t E, const void* C, const double* n, mp
       hipLaunchKernelGGL(jointd_sum_f64, dim3((unsigned)items), dim3(256), 0, stream, p, tau,
                          (const double*)tables, band, acc);
   } else {
-    if (part)
-      hipLaunchKernelGGL((jointd_occupations<float, true>), dim3(blocks), dim3(256), 0, stream, p,
-                         (const float*)nullptr, part, n, rec);
-    else
-      hipLaunchKernelGGL((jointd_occupations<float, false>), dim3(blocks), dim3(256), 0, stream,
-                         p, (const float*)C, (const float*)nullptr, n, rec);
     const mp_status sb = record_bands_launch(rec, E, d, K, kJD, band, stream);
     if (sb != MP_OK) return sb;
     hipLaunchKernelGGL(jointd_factors<float>, fgrid, dim3(256), 0, stream, p, rec, band,
                        (float*)tables);
     for (int tau = 0; tau < 2; ++tau)
-      hipLaunchKernelGGL((p.d == 3 ? jointd_sum_f32<3> : jointd_sum_f32<4>), dim3((unsigned)items), dim3(256), 0, stream, p, tau,
-                         (const float*)tables, band, acc);
+      hipLaunchKernelGGL((p.d == 3 ? jointd_sum_f32<3> : jointd_sum_f32<4>), dim3((unsigned)items),
+                         dim3(256), 0, stream, p, tau, (const float*)tables, band, acc);
   }
   MP_HIP_LAUNCH_CHECK("mp_binned_counts joint (d >= 3) launch");
   return MP_OK;

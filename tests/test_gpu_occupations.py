@@ -95,3 +95,37 @@ def test_counts_on_both_sides_of_the_row_line(prec, M, E):
     u, arg = (2.0 ** -24, 46.0) if prec == "fp32" else (2.0 ** -53, 46 + 32 * 20 + M)
     got = acc.cpu().numpy().view(complex)
     assert np.all(np.abs(got - ref[0]) <= 2 * (arg + 16) * u * mag[0] + E * np.exp(-46.0))
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("d,M", [(2, 61), (2, 301), (3, 97), (3, 461)])
+@pytest.mark.parametrize("E", [1, 6, 35])
+def test_joint_sums_by_rows_and_waves(prec, d, M, E):
+    """Joint sums of bins of some 30 and 150 modes (a row of lanes and a wave per sample).  The
+    bound is the joint tests', with the bin sums' own (M u) in FP64."""
+    import torch
+
+    import paper_2503_12749_amd as mp
+    from test_gpu_jointd_tiles import _sums
+    rng = np.random.default_rng(M + E)
+    dt = np.float64 if prec == "fp64" else np.float32
+    w = (M - 1) // d
+    bins = _bins(M, [(1 + q * w, 1 + (q + 1) * w, q) for q in range(d)])
+    ldm = mp.mp_ld_modes(M)
+    C = np.full((2 * E, 2, ldm), np.nan, dtype=dt)
+    C[:, :, :M] = (rng.standard_normal((2 * E, 2, M)) / np.sqrt(M)).astype(dt)
+    C[:, 0, :M] += dt(3 / np.sqrt(M))
+    C[:, :, 0] = np.nan
+    X = C[:, :, :M].astype(np.float64)
+    nj = (X[:E, 0] + 1j * X[:E, 1]) * (X[E:, 0] - 1j * X[E:, 1])
+    occ = np.stack([nj[:, bins == q].sum(1) for q in range(d)])
+    n = occ.real.sum(0) * 1.05
+    K = (12, 9, 10)[:d]
+    acc = torch.zeros(int(np.prod(K)) * 2, dtype=torch.float64, device="cuda")
+    ws = torch.empty(mp.mp_binned_workspace(d, "joint", K, E, 1, E, 0), dtype=torch.uint8, device="cuda")
+    mp.mp_binned_counts(M, E, torch.from_numpy(C.reshape(-1)).cuda(), torch.from_numpy(n).cuda(), prec,
+                        "matrix_p", d, bins, "joint", (0, 0, 0)[:d], K, 1, E, 0, acc, ws)
+    ref, mag = _sums(occ, n, K, (0, 0, 0)[:d], 0, E, 1, False)
+    u, arg = (2.0 ** -24, 46 + 2 * 12) if prec == "fp32" else (2.0 ** -53, 46 + 8 * 12 + M)
+    got = acc.cpu().numpy().view(complex).reshape((1,) + K)
+    assert np.all(np.abs(got - ref) <= (d * (arg + 16) + 2 * E) * u * mag + E * np.exp(-46.0))
