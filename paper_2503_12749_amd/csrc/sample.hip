@@ -33,12 +33,11 @@ constexpr uint64_t kMul0 = 0xD2E7470EE14C6C93ull, kMul1 = 0xCA5A826395121157ull;
 constexpr uint64_t kWeyl0 = 0x9E3779B97F4A7C15ull, kWeyl1 = 0xBB67AE8584CAA73Bull;
 
 // Full 128-bit product of two 64-bit words from four 32 x 32 -> 64
-// multiply-adds: a b = p00 + (a0 b1 + a1 b0) 2^32 + a1 b1 2^64.
-// mulhilo64 leaves the form to the compiler (wave-uniform operands run on the
-// scalar unit); mulhilo64_vec is the vector form: the middle sum takes its
-// carry from v_mad_u64_u32 itself and the words meet in one carry chain, four
-// multiply-adds and four adds (the compiler's form adds about five moves, for
-// the zero-extended 64-bit addends).
+// multiply-adds: a b = p00 + (a0 b1 + a1 b0) 2^32 + a1 b1 2^64.  The form is left to
+// the compiler: wave-uniform operands run on the scalar unit, and the vector form adds
+// 64-bit words without carry masks.  A hand-written carry chain of four adds has about
+// five moves less, but gfx950 wants two wait states between a carry and its reader, which
+// cost more (65536 samples of M = 8000: 2.75 ms with them, 2.60 without the chain).
 __device__ inline void mulhilo64(uint64_t a, uint64_t b, uint64_t& hi, uint64_t& lo) {
   const uint32_t a0 = (uint32_t)a, a1 = (uint32_t)(a >> 32);
   const uint32_t b0 = (uint32_t)b, b1 = (uint32_t)(b >> 32);
@@ -47,25 +46,6 @@ __device__ inline void mulhilo64(uint64_t a, uint64_t b, uint64_t& hi, uint64_t&
   const uint64_t t2 = (uint64_t)a1 * b0 + (uint32_t)t1;
   hi = (uint64_t)a1 * b1 + (t1 >> 32) + (t2 >> 32);
   lo = (t2 << 32) | (uint32_t)p00;
-}
-
-__device__ inline void mulhilo64_vec(uint64_t a, uint64_t b, uint64_t& hi, uint64_t& lo) {
-  const uint32_t a0 = (uint32_t)a, a1 = (uint32_t)(a >> 32);
-  const uint32_t b0 = (uint32_t)b, b1 = (uint32_t)(b >> 32);
-  const uint64_t p00 = (uint64_t)a0 * b0, p01 = (uint64_t)a0 * b1, p11 = (uint64_t)a1 * b1;
-  uint64_t mid, carry;  // a1 b0 + p01 and its carry (lane mask)
-  asm("v_mad_u64_u32 %0, %1, %2, %3, %4" : "=v"(mid), "=s"(carry) : "s"(a1), "v"(b0), "v"(p01));
-  uint32_t l1, h0, h1;
-  asm("v_add_co_u32 %0, vcc, %3, %4\n\t"
-      "v_addc_co_u32 %1, vcc, %5, %6, vcc\n\t"
-      "v_addc_co_u32 %2, vcc, 0, %7, vcc\n\t"
-      "v_addc_co_u32 %2, vcc, 0, %2, %8"
-      : "=&v"(l1), "=&v"(h0), "=&v"(h1)
-      : "v"((uint32_t)(p00 >> 32)), "v"((uint32_t)mid), "v"((uint32_t)p11),
-        "v"((uint32_t)(mid >> 32)), "v"((uint32_t)(p11 >> 32)), "s"(carry)
-      : "vcc");
-  lo = ((uint64_t)l1 << 32) | (uint32_t)p00;
-  hi = ((uint64_t)h1 << 32) | h0;
 }
 
 // a ^ b ^ c, one v_bitop3_b32 per half
@@ -82,8 +62,8 @@ __device__ inline void philox_rounds(int from, uint64_t& c0, uint64_t& c1, uint6
 #pragma unroll
   for (int round = from; round < 10; ++round) {
     uint64_t hi0, lo0, hi1, lo1;
-    mulhilo64_vec(kMul0, c0, hi0, lo0);
-    mulhilo64_vec(kMul1, c2, hi1, lo1);
+    mulhilo64(kMul0, c0, hi0, lo0);
+    mulhilo64(kMul1, c2, hi1, lo1);
     c0 = xor3(hi1, c1, k0 + (uint64_t)round * kWeyl0);
     c1 = lo1;
     c2 = xor3(hi0, c3, k1 + (uint64_t)round * kWeyl1);
@@ -119,10 +99,10 @@ __device__ inline PhiloxHead philox_head(uint64_t g, uint64_t net, uint64_t seed
 __device__ inline void philox_lane(const PhiloxHead& h, uint32_t p, uint64_t seed, uint64_t& c0,
                                    uint64_t& c1, uint64_t& c2, uint64_t& c3) {
   uint64_t hi, lo;
-  mulhilo64_vec(kMul0, h.c0 ^ p, hi, lo);  // round 1
+  mulhilo64(kMul0, h.c0 ^ p, hi, lo);  // round 1
   c2 = hi ^ h.m2;
   c3 = lo;
-  mulhilo64_vec(kMul1, c2, hi, lo);  // round 2
+  mulhilo64(kMul1, c2, hi, lo);  // round 2
   c0 = hi ^ h.a;
   c1 = lo;
   c2 = c3 ^ h.b;
@@ -443,8 +423,8 @@ __device__ inline double sample_pair(int M, int64_t ldm, int64_t E, void* __rest
 // products whose operands do not depend on the lane yet, both of round 1 and
 // one of rounds 2 and 3, to the scalar unit: 4 of 20.  Bound by the vector
 // ALU: Philox (64-bit multiply-adds at half rate) and the FP64 series about
-// equally.  65536 samples of M = 8000: 2.99 ms (3.17 GB written, the
-// FP8-correction form) against 4.13 ms with per-wave coefficients and
+// equally.  65536 samples of M = 8000: 2.60 ms (3.17 GB written, the
+// FP8-correction form) against 3.68 ms with per-wave coefficients and
 // the sample index in a vector register.
 constexpr int kSampleWaves = 8, kSampleMax = 4;
 template <int PREC>
