@@ -136,6 +136,13 @@ __host__ __device__ inline int64_t pair8_offset(int64_t r, int64_t j, int64_t ld
   return (r >> 1) * 2 * ldm + 128 * (j >> 6) + 64 * (r & 1) + (j & 63);
 }
 
+// The i-th word to read of the `bytes` at p (any address) to touch each of their 128-byte
+// lines: an aligned 4-byte word that lies wholly inside them, null past the last.
+__host__ __device__ inline const char* touch_word(const void* p, int64_t bytes, int64_t i) {
+  const char* q = (const char*)(((uintptr_t)p + 3) & ~(uintptr_t)3) + 128 * i;
+  return q + 4 <= (const char*)p + bytes ? q : nullptr;
+}
+
 // v of the lane that the DPP control names, for both halves of a double.
 template <int CTRL>
 __device__ inline double dpp_f64(double v) {

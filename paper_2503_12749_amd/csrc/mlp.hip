@@ -384,10 +384,10 @@ __global__ __launch_bounds__(kMlpThreads) void mlp_rows(MlpNet p, const uint16_t
   // layers run, instead of one memory latency per layer.
   {
     const int64_t n = p.off[p.L - 1] + (int64_t)(p.width[p.L - 1] + 1) * p.width[p.L];
-    const char* w0 = (const char*)((uintptr_t)w16 & ~(uintptr_t)3);
     lds_void* sink = (lds_void*)(sums + kMlpSums);
-    for (int64_t o = (int64_t)tid * 128; o + 4 <= 2 * n; o += (int64_t)kMlpThreads * 128)
-      __builtin_amdgcn_global_load_lds((const void*)(w0 + o), sink, 4, 0, 0);
+    const char* q;
+    for (int64_t i = tid; (q = touch_word(w16, 2 * n, i)) != nullptr; i += kMlpThreads)
+      __builtin_amdgcn_global_load_lds((const void*)q, sink, 4, 0, 0);
   }
   for (int n = n8; n < ((p.width[0] + 31) & ~31); n += kMlpPass) {
     float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
