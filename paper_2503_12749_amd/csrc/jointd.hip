@@ -558,15 +558,14 @@ __global__ __launch_bounds__(256) void jointd_sum_f64(JointDParams p, int tau,
 // A + B products per point instead of K (A: the largest divisor up to 16 and
 // sqrt(K); a K without one takes the sum directly, A = 1, over the k where a
 // line is not zero).  A thread forms several outputs of a sum from one pass
-// over its terms: a term times its step twiddle per output, a chain of at most
-// 16 rotations from an exact twiddle.  A workgroup holds G lines in LDS,
+// over its terms (OUT of the second sum): a term times its step twiddle per output, a
+// chain of at most 16 rotations from an exact twiddle.  A workgroup holds G lines in LDS,
 // neighbours along the contiguous dimension, one padding element per B so that
 // both steps read without bank conflicts; step 1 works in place.  Workgroups
 // whose lines are all zero (outside the boxes) write zeros.  Bound by the FP64
 // operations and the L2 traffic about equally; one line or two per workgroup
 // with K products per point, one sub-ensemble per launch, took 153 us per axis
-// and sub-ensemble for 128^3 points and 111 us for 1024^2 (now 38 to 46 and 37
-// to 54 us).
+// and sub-ensemble for 128^3 points and 111 us for 1024^2 (now 36 and 49 us).
 //
 // in and out hold `subs` grids: blockIdx.y for the inner axes; on the last
 // axis a workgroup takes its lines of every sub-ensemble in order, and the
@@ -574,13 +573,21 @@ __global__ __launch_bounds__(256) void jointd_sum_f64(JointDParams p, int tau,
 // squared deviations (m2) with Welford's update.
 struct AxisParams {
   int K, A, B, G, GP;  // GP: lines' LDS stride (odd)
+  int out;             // outputs per thread of the second sum: 8 or 1
   int64_t n_lines, stride, cells;
   double scale;
   int s0, subs;
 };
 constexpr int kAxisA = 16;    // longest first sum
-constexpr int kAxisOut = 8;   // outputs per thread of the second sum
 constexpr int kAxisPoints = 2048;  // points per workgroup (G lines), where K allows
+// Small grids are bound by the latency of a workgroup instead: a workgroup then holds as few
+// lines as leave kAxisGroups workgroups (of at least 128 points), and where the second sum
+// has less than 128 items of eight outputs a thread forms one output, of terms loaded four
+// at a time, and the first sum is at most four long.  Three launches and one
+// sub-ensemble, by 2048 points and eight outputs against so: 64 x 64 points 31 and 20 us, 97 x 89
+// 52 and 20, 256 x 256 56 and 22, 24^3 37 and 24, 4 x 4 x 500 49 and 29; at 512 x 512 the
+// rule changes nothing (63 us), and one output a thread would take longer.
+constexpr int kAxisGroups = 256;
 constexpr int kAxisMaxSubs = 1024;  // sub-ensembles per launch
 
 // x / d for 0 <= x < 2^22 and 1 <= d: the FP32 estimate is at most one off
@@ -590,7 +597,7 @@ __device__ inline int fast_div(int x, int d, float inv_d) {
   return q + (r >= d ? 1 : 0) - (r < 0 ? 1 : 0);
 }
 
-template <bool LAST>
+template <bool LAST, int OUT>
 __global__ __launch_bounds__(256) void jointd_axis(AxisParams p, const double* __restrict__ in,
                                                    double* __restrict__ out,
                                                    double* __restrict__ P_re,
@@ -603,14 +610,16 @@ __global__ __launch_bounds__(256) void jointd_axis(AxisParams p, const double* _
   d2* buf = (d2*)smem;                  // (K + A) x GP
   d2* tw = buf + (int64_t)(K + A) * GP;  // e^{-2 pi i q / B}, q < B
   d2* twa = tw + B;                      // e^{-2 pi i q / A}, q < A
-  int* nzb = (int*)(twa + A);            // any line nonzero at k = b mod B
+  d2* twk = twa + A;                     // A > 1: e^{-2 pi i q / K}, q < B
+  int* nzb = (int*)(twk + (A > 1 ? B : 0));  // any line nonzero at k = b mod B
   const int tid = threadIdx.x;
   const int64_t L0 = (int64_t)blockIdx.x * G;
   const int nl = p.n_lines - L0 < G ? (int)(p.n_lines - L0) : G;
   const float inv_k = 1.0f / (float)K, inv_b = 1.0f / (float)B, inv_g = 1.0f / (float)G;
-  for (int i = tid; i < B + A; i += 256) {
+  for (int i = tid; i < B + A + (A > 1 ? B : 0); i += 256) {
+    const int q = i < B ? i : (i < B + A ? i - B : i - B - A);
     double sw, cw;
-    sincospi(i < B ? -2.0 * ((double)i / B) : -2.0 * ((double)(i - B) / A), &sw, &cw);
+    sincospi(-2.0 * ((double)q / (i < B ? B : (i < B + A ? A : K))), &sw, &cw);
     tw[i] = d2{cw, sw};
   }
   // first element of line g (its elements are p.stride apart)
@@ -664,21 +673,20 @@ __global__ __launch_bounds__(256) void jointd_axis(AxisParams p, const double* _
             vr = t;
           }
         }
-        double sb, cb;
-        sincospi(-2.0 * ((double)b / K), &sb, &cb);
+        const d2 wk = twk[b];
         double wr = 1.0, wi = 0.0;
 #pragma unroll
         for (int u = 0; u < kAxisA; ++u) {
           if (u >= A) break;
           x[u * pitch] = d2{fma(zr[u], wr, -(zi[u] * wi)), fma(zr[u], wi, zi[u] * wr)};
-          const double t = fma(wr, cb, -(wi * sb));
-          wi = fma(wr, sb, wi * cb);
+          const double t = fma(wr, wk.x, -(wi * wk.y));
+          wi = fma(wr, wk.y, wi * wk.x);
           wr = t;
         }
       }
       __syncthreads();
     }
-    const int AG = A * G, nj = (B + kAxisOut - 1) / kAxisOut;
+    const int AG = A * G, nj = (B + OUT - 1) / OUT;
     const float inv_ag = 1.0f / (float)AG, inv_a = 1.0f / (float)A;
     for (int it = tid; it < AG * nj; it += 256) {
       const int j = fast_div(it, AG, inv_ag), r = it - j * AG;
@@ -690,35 +698,55 @@ __global__ __launch_bounds__(256) void jointd_axis(AxisParams p, const double* _
         l1 = fast_div(r, G, inv_g);
         g = r - l1 * G;
       }
-      double sr[kAxisOut], si[kAxisOut];
+      double sr[OUT], si[OUT];
 #pragma unroll
-      for (int u = 0; u < kAxisOut; ++u) sr[u] = si[u] = 0.0;
+      for (int u = 0; u < OUT; ++u) sr[u] = si[u] = 0.0;
       if (any) {
         const d2* z = buf + l1 * (B + 1) * GP + g;
-        const int l0 = j * kAxisOut;  // < B
-        int q = 0;                    // b l0 mod B
-        for (int b = 0; b < B; ++b) {
-          if (nzb[b]) {
-            const d2 v = z[b * GP], w0 = tw[q], w = tw[b];
-            double vr = fma(v.x, w0.x, -(v.y * w0.y)), vi = fma(v.x, w0.y, v.y * w0.x);
+        const int l0 = j * OUT;  // < B
+        int q = 0;               // b l0 mod B
+        if constexpr (OUT == 1) {
+          // four terms at a time, their loads together; those past B count as zero
+          for (int b = 0; b < B; b += 4) {
+            d2 v[4], w[4];
 #pragma unroll
-            for (int u = 0; u < kAxisOut; ++u) {
-              sr[u] += vr;
-              si[u] += vi;
-              const double t = fma(vr, w.x, -(vi * w.y));
-              vi = fma(vr, w.y, vi * w.x);
-              vr = t;
+            for (int e = 0; e < 4; ++e) {
+              v[e] = z[min(b + e, B - 1) * GP];
+              w[e] = tw[q];
+              q += l0;
+              q -= q >= B ? B : 0;
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const double xr = b + e < B ? v[e].x : 0.0, xi = b + e < B ? v[e].y : 0.0;
+              sr[0] += fma(xr, w[e].x, -(xi * w[e].y));
+              si[0] += fma(xr, w[e].y, xi * w[e].x);
             }
           }
-          q += l0;
-          q -= q >= B ? B : 0;
+        } else {
+          for (int b = 0; b < B; ++b) {
+            if (nzb[b]) {
+              const d2 v = z[b * GP], w0 = tw[q], w = tw[b];
+              double vr = fma(v.x, w0.x, -(v.y * w0.y)), vi = fma(v.x, w0.y, v.y * w0.x);
+#pragma unroll
+              for (int u = 0; u < OUT; ++u) {
+                sr[u] += vr;
+                si[u] += vi;
+                const double t = fma(vr, w.x, -(vi * w.y));
+                vi = fma(vr, w.y, vi * w.x);
+                vr = t;
+              }
+            }
+            q += l0;
+            q -= q >= B ? B : 0;
+          }
         }
       }
       if (g >= nl) continue;
       const int64_t base = LAST ? (L0 + g) * K : line_base(g);
 #pragma unroll
-      for (int u = 0; u < kAxisOut; ++u) {
-        const int l2 = j * kAxisOut + u;
+      for (int u = 0; u < OUT; ++u) {
+        const int l2 = j * OUT + u;
         if (l2 >= B) break;
         const int64_t cell = base + (l1 + A * l2) * p.stride;
         if constexpr (!LAST) {
@@ -757,22 +785,27 @@ int64_t round_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
 AxisParams axis_params(int32_t d, const int32_t* K, int a, int64_t cells) {
   AxisParams p{};
   p.K = K[a];
-  p.A = 1;
-  for (int f = 2; f <= kAxisA && f * f <= p.K; ++f)
-    if (p.K % f == 0) p.A = f;
-  p.B = p.K / p.A;
   p.stride = 1;
   for (int b = a + 1; b < d; ++b) p.stride *= K[b];
   p.cells = cells;
   p.n_lines = cells / p.K;
   p.G = 1;
   while (p.G < 64 && 2 * p.G * p.K <= kAxisPoints) p.G *= 2;
+  while (p.G > 1 && (p.n_lines + p.G - 1) / p.G < kAxisGroups && p.G * p.K >= 256) p.G /= 2;
+  for (p.out = 8;; p.out = 1) {
+    p.A = 1;
+    for (int f = 2; f <= (p.out == 8 ? kAxisA : 4) && f * f <= p.K; ++f)
+      if (p.K % f == 0) p.A = f;
+    p.B = p.K / p.A;
+    if (p.out == 1 || p.G * p.A * ((p.B + 7) / 8) >= 128) break;
+  }
   p.GP = p.G == 1 ? 1 : p.G + 1;
   return p;
 }
 
 size_t axis_lds(const AxisParams& p) {
-  return (size_t)(p.K + p.A) * p.GP * 16 + (size_t)(p.A + p.B) * 16 + (size_t)p.B * 4;
+  return (size_t)(p.K + p.A) * p.GP * 16 + (size_t)(p.A + p.B + (p.A > 1 ? p.B : 0)) * 16 +
+         (size_t)p.B * 4;
 }
 // the largest: one line of a prime K below kAxisMaxK
 constexpr int kAxisMaxLds = (kAxisMaxK + 1) * 16 + (kAxisMaxK + 1) * 16 + kAxisMaxK * 4;
@@ -945,7 +978,8 @@ mp_status jointd_finalize(int32_t d, const int32_t* K, int32_t n_sub, int64_t ns
                  kmax, b, K[b]);
   static bool lds_set = false;
   if (!lds_set) {
-    for (const void* k : {(const void*)jointd_axis<false>, (const void*)jointd_axis<true>}) {
+    for (const void* k : {(const void*)jointd_axis<false, 8>, (const void*)jointd_axis<true, 8>,
+                          (const void*)jointd_axis<false, 1>, (const void*)jointd_axis<true, 1>}) {
       const hipError_t e =
           hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kAxisMaxLds);
       MP_CHECK_ARG(e == hipSuccess, MP_ERR_HIP, "mp_counts_finalize: %s", hipGetErrorString(e));
@@ -973,10 +1007,11 @@ mp_status jointd_finalize(int32_t d, const int32_t* K, int32_t n_sub, int64_t ns
       double* dst = buf[a & 1];
       const unsigned groups = (unsigned)((p.n_lines + p.G - 1) / p.G);
       if (a == d - 1)
-        hipLaunchKernelGGL(jointd_axis<true>, dim3(groups), dim3(256), axis_lds(p), stream, p, src,
+        hipLaunchKernelGGL((p.out == 8 ? jointd_axis<true, 8> : jointd_axis<true, 1>), dim3(groups), dim3(256), axis_lds(p), stream, p, src,
                            (double*)nullptr, P_re, P_im, sigma);
       else
-        hipLaunchKernelGGL(jointd_axis<false>, dim3(groups, (unsigned)p.subs), dim3(256),
+        hipLaunchKernelGGL((p.out == 8 ? jointd_axis<false, 8> : jointd_axis<false, 1>),
+                           dim3(groups, (unsigned)p.subs), dim3(256),
                            axis_lds(p), stream, p, src, dst, (double*)nullptr, (double*)nullptr,
                            (double*)nullptr);
       src = dst;
