@@ -74,7 +74,7 @@ struct MlpNet {
 // are handed out in double precision: they keep their values to the last bit.
 constexpr int MLP_T = 64, MLP_THREADS = 256;
 
-// KC: depth of a staged K chunk (32 for layers of up to 32 inputs, else 128).  Bound by the
+// KC: depth of a staged K chunk (mlp_forward has the rule).  Bound by the
 // latency of a chunk: its loads are all issued before the first is used, and the deeper
 // chunk takes a quarter of the turns.  512 rows, layers of 5, 208, 55, 307, 51 and 8:
 // 11.2 us a layer of more than 32 inputs (20.4 us with 32-deep chunks loaded as used).
@@ -656,7 +656,11 @@ mp_status mlp_forward(const mp_mlp_shape* s, const uint16_t* w16, const float* p
     // one layer reads X while it writes: through the workspace, as Y may be X
     float* act = last && l > 0 ? Y : cur;
     cur += (int64_t)batch * O;
-    const int KC = I <= 32 ? 32 : 128;
+    const int64_t groups = (int64_t)((batch + MLP_T - 1) / MLP_T) * ((O + MLP_T - 1) / MLP_T);
+    // the deep chunk's LDS leaves two workgroups per CU: from a full turn of them on, shallow
+    // chunks overlap more (the sums are in the same order): layers of 5, 256, 256, 256 and 8,
+    // 131072 rows: 848 us deep, 381 us shallow; 4096 rows 45 us deep, 91 us before deep chunks
+    const int KC = I <= 32 || groups >= 512 ? 32 : 128;
     auto kernel = KC == 32 ? mlp_layer<32> : mlp_layer<128>;
     const size_t lds = (size_t)4 * MLP_T * (KC + 8) * 2;
     const mp_status r = mlp_lds((const void*)kernel, lds);
