@@ -486,6 +486,7 @@ __global__ __launch_bounds__(64 * kSampleWaves) void sample_kernel(
 // samples are then cleared by the whole wave.  1e4 samples of M = 16 in FP64:
 // 14 us against 44 us with one sample per wave at a time.
 constexpr int kSmallModes = 64;
+constexpr int kSmallLd = kLdAlign;  // their row stride
 
 template <int PREC>
 __global__ __launch_bounds__(256) void sample_small(int M, int64_t ldm, int64_t g0, int64_t E,
@@ -505,39 +506,44 @@ __global__ __launch_bounds__(256) void sample_small(int M, int64_t ldm, int64_t 
     n = sample_pair<PREC>(M, ldm, E, ab, k, p, c0, c1, c2, c3, cf);
   }
   for (int off = lps >> 1; off > 0; off >>= 1) n += __shfl_xor(n, off, 64);
-  if (!valid) return;
-  if (p == 0) n_out[k] = n;
-  // zero modes [2 lps, ldm): both columns' 16-byte pieces
-  auto clear = [&](char* col, int64_t lo, int64_t hi) {
-    typedef __attribute__((ext_vector_type(2))) uint64_t u64x2;
-    for (int64_t o = lo + 16 * p; o < hi; o += 16 * lps) *(u64x2*)(col + o) = u64x2{0, 0};
+  if (valid && p == 0) n_out[k] = n;
+  // the padding modes [2 lps, ldm) of the wave's samples by the whole wave, in storage
+  // order: pieces V of `bytes` bytes from base on, where a sample (or the two of a pair, or
+  // the hi and lo values of one: SIDES) has runs of RUN modes in turn.  The wave's pieces
+  // are whole samples or pairs, so a lane's modes are the same on every turn
+  const int64_t k0 = k - lane / lps;
+  auto clear = [&](auto piece, auto run, auto sides, char* base, uint32_t bytes) {
+    typedef decltype(piece) V;
+    constexpr uint32_t RUN = decltype(run)::value, SIDES = decltype(sides)::value;
+    constexpr uint32_t el = F64 ? 8 : (PREC == MP_FP32 ? 4 : (sizeof(V) == 4 ? 1 : 2));
+    constexpr uint32_t turn = 64 * sizeof(V), group = SIDES * kSmallLd;
+    static_assert(turn % (group * el) == 0, "whole samples");
+    const uint32_t e = lane * (uint32_t)sizeof(V) / el % group;
+    if (e / (RUN * SIDES) * RUN + e % RUN < 2u * lps) return;
+    for (uint32_t o = lane * sizeof(V); o < bytes; o += turn) *(V*)(base + o) = V{};
   };
-  const int64_t used = 2 * lps;
-  if constexpr (PREC == MP_FP64 || PREC == MP_FP32) {
-    constexpr int sz = F64 ? 8 : 4;
-    clear((char*)ab + k * ldm * sz, used * sz, ldm * sz);
-    clear((char*)ab + (E + k) * ldm * sz, used * sz, ldm * sz);
-  } else {
-    // 16-bit values in 64-byte runs of 32 modes, 128 bytes apart: the hi and the lo
-    // values of a column (split), or the columns of a pair (T-split)
-    constexpr bool kPair = PREC == MP_SPLIT1T_FP16 || PREC == MP_SPLIT1T_F8;
-    const int64_t e2 = kPair ? split1t_half(E) : E;
-    const bool last_odd = kPair && (E & 1) && k == E - 1;  // clears its padding column too
-    typedef __attribute__((ext_vector_type(2))) uint16_t u16x2;
-    for (int64_t j = used + 2 * p; j < ldm; j += 2 * lps)
+  typedef __attribute__((ext_vector_type(2))) uint64_t u64x2;
+  constexpr bool kPair = PREC == MP_SPLIT1T_FP16 || PREC == MP_SPLIT1T_F8;
+  const int64_t half = kPair ? split1t_half(E) : E, left = half - k0;
+  if (left <= 0) return;
+  const uint32_t nc = left < 64 / lps ? (uint32_t)left : 64u / lps;
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int64_t c = h ? e2 + k : k;
-        uint16_t* q = (uint16_t*)ab + (kPair ? split1t_offset(c, j, ldm)
-                                             : c * 2 * ldm + 64 * (j >> 5) + (j & 31));
-        *(u16x2*)q = u16x2{0, 0};
-        if (!kPair || last_odd) *(u16x2*)(q + 32) = u16x2{0, 0};
-        if constexpr (PREC == MP_SPLIT1T_F8) {
-          uint8_t* b = (uint8_t*)ab + 4 * e2 * ldm + pair8_offset(c, j, ldm);
-          *(uint16_t*)b = 0;
-          if (last_odd) *(uint16_t*)(b + 64) = 0;
-        }
-      }
+  for (int h = 0; h < 2; ++h) {
+    const int64_t c0 = (h * half + k0) * kSmallLd;
+    if constexpr (F64 || PREC == MP_FP32) {
+      constexpr uint32_t sz = F64 ? 8 : 4;
+      clear(u64x2{}, std::integral_constant<uint32_t, kSmallLd>{}, std::integral_constant<uint32_t, 1>{},
+            (char*)ab + c0 * sz, nc * kSmallLd * sz);
+    } else {
+      // runs of 32 16-bit values: the hi and the lo ones of a column (split), or the two
+      // columns of a pair (T-split; the first column of a wave and of either half is even)
+      constexpr uint32_t sz = kPair ? 2 : 4;
+      clear((uint64_t)0, std::integral_constant<uint32_t, 32>{}, std::integral_constant<uint32_t, 2>{},
+            (char*)ab + c0 * sz, nc * kSmallLd * sz);
+      if constexpr (PREC == MP_SPLIT1T_F8)
+        clear((uint32_t)0, std::integral_constant<uint32_t, 64>{}, std::integral_constant<uint32_t, 2>{},
+              (char*)ab + 4 * half * kSmallLd + c0, nc * kSmallLd);
+    }
   }
 }
 
