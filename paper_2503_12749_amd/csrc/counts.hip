@@ -1459,8 +1459,11 @@ struct SampleStatParams {
 // per sample n_q^k, times tanh(n) for odd k on the matrix-P path (+P: 1).
 // Block (s, q): the chunk's samples of sub-ensemble s_first + blockIdx.x,
 // summed in a fixed order (strided per thread, then over the waves) and added to
-// acc[s][q][k - 1] (re, im).  Few workgroups, each a chain of a thread's samples: 1024
-// threads a workgroup (1e4 samples per sub-ensemble, one bin: 22 us, 43 us with 256).
+// acc[s][q][k - 1] (re, im).  Bound by the chain of a thread's samples where there
+// are few workgroups, then by the reductions over their waves: the least threads, 64 to
+// 1024, that leave a thread four samples, 256 where more than 512 workgroups fill the CUs
+// (1e5 samples, one bin: 22 us in sub-ensembles of 1e4, 43 us with 256 threads; 8 us in
+// sub-ensembles of 100, 17 us with 1024 threads; 1e6 samples, nine bins, 1e4: 127 and 151 us).
 constexpr int kMomentThreads = 1024;
 __global__ __launch_bounds__(kMomentThreads) void moments_kernel(SampleStatParams p,
                                                                  const double* __restrict__ n,
@@ -1475,7 +1478,7 @@ __global__ __launch_bounds__(kMomentThreads) void moments_kernel(SampleStatParam
   double sr[MP_MAX_MOMENTS], si[MP_MAX_MOMENTS];
 #pragma unroll
   for (int o = 0; o < MP_MAX_MOMENTS; ++o) sr[o] = si[o] = 0.0;
-  for (int64_t g = lo + threadIdx.x; g < hi; g += kMomentThreads) {
+  for (int64_t g = lo + threadIdx.x; g < hi; g += blockDim.x) {
     const int64_t k = g - p.e0;
     const double zr = nq[(k * p.n_dist + q) * 2], zi = nq[(k * p.n_dist + q) * 2 + 1];
     double w = 1.0;  // +P
@@ -1510,7 +1513,7 @@ __global__ __launch_bounds__(kMomentThreads) void moments_kernel(SampleStatParam
   if ((int)threadIdx.x < 2 * p.kmax) {
     const int o = threadIdx.x >> 1, c = threadIdx.x & 1;
     double t = 0.0;
-    for (int w = 0; w < kMomentThreads / 64; ++w) t += red[w][o][c];
+    for (int w = 0; w < (int)blockDim.x / 64; ++w) t += red[w][o][c];
     acc[((s * p.n_dist + q) * p.kmax + o) * 2 + c] += t;
   }
 }
@@ -1650,9 +1653,12 @@ mp_status moments_launch(int64_t E, const double* n, const double* nq, int32_t n
   p.n_dist = n_dist;
   p.est = est;
   p.kmax = kmax;
-  const int64_t n_touched = (e0 + E - 1) / ns - p.s_first + 1;
-  hipLaunchKernelGGL(moments_kernel, dim3((unsigned)n_touched, (unsigned)n_dist),
-                     dim3(kMomentThreads), 0, stream, p, n, nq, acc);
+  const int64_t n_touched = (e0 + E - 1) / ns - p.s_first + 1, len = ns < E ? ns : E;
+  int threads = 64;
+  const int most = n_touched * n_dist > 512 ? 256 : kMomentThreads;
+  while (threads < most && threads * 4 < len) threads *= 2;
+  hipLaunchKernelGGL(moments_kernel, dim3((unsigned)n_touched, (unsigned)n_dist), dim3(threads), 0,
+                     stream, p, n, nq, acc);
   MP_HIP_LAUNCH_CHECK("mp_moments_accumulate launch");
   return MP_OK;
 }
