@@ -1520,9 +1520,7 @@ __global__ __launch_bounds__(kMomentThreads) void moments_kernel(SampleStatParam
 
 // Per-sample count observable of distribution q at count m (eq.
 // c-number-variable for one bin: g0 n_q^m e^{-n_q} / m!, with g0 formed as in
-// counts_fused; +P: n_q^m e^{-n_q} / m!), real part, binned into n_bins equal
-// bins from o_min (bin 0: below, bin n_bins + 1: at or above the top or not
-// finite).  Counts are added as FP64 ones, exact and order-independent.
+// counts_fused; +P: n_q^m e^{-n_q} / m!), real part, in n_bins equal bins from o_min.
 // Bin of chunk sample k (0: below the range, n_bins + 1: above it or not finite).
 __device__ inline int64_t histogram_bin(const SampleStatParams& p, const double* __restrict__ n,
                                         const double* __restrict__ nq, int64_t k) {
@@ -1559,34 +1557,42 @@ __device__ inline int64_t histogram_bin(const SampleStatParams& p, const double*
   return x < 0.0 ? 0 : (x >= (double)p.n_bins ? p.n_bins + 1 : (int64_t)x + 1);
 }
 
-// A workgroup counts its 256 per samples (per = 1 .. 8, as E leaves some 256 workgroups) in LDS and adds its bins once, where the bins
-// fit and the samples are of one sub-ensemble; else each sample is added by itself.
-// Counts are whole numbers, so both give the same sums.  One FP64 atomic per sample was
-// bound by the turns at the few bins that are hit (1e5 samples, 100 bins: 58 us, now 9 us).
+// ONE: a sample per thread, each added by itself.  Else a workgroup counts its 256 per
+// samples in LDS and adds its bins once, where the bins fit and the samples are of one
+// sub-ensemble.  Counts are whole numbers, so both give the same sums.  One FP64 atomic per
+// sample is bound by the turns at the few bins that are hit (1e5 samples, 100 bins: 58 us,
+// 9 us counted in LDS); histogram_launch has the rule.
 constexpr int kHistBins = 4096;
+template <bool ONE>
 __global__ __launch_bounds__(256) void histogram_kernel(SampleStatParams p, const double* __restrict__ n,
                                                         const double* __restrict__ nq,
                                                         double* __restrict__ hist) {
-  __shared__ int counts[kHistBins];
-  const int64_t k0 = (int64_t)blockIdx.x * (256 * p.per);
-  const int64_t k1 = k0 + 256 * p.per < p.E ? k0 + 256 * p.per : p.E;
-  const int64_t s = (p.e0 + k0) / p.ns;
-  const bool local = p.n_bins + 2 <= kHistBins && s == (p.e0 + k1 - 1) / p.ns;
-  if (local) {
-    for (int i = threadIdx.x; i < p.n_bins + 2; i += 256) counts[i] = 0;
+  if constexpr (ONE) {
+    const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (k >= p.E) return;
+    atomicAdd(hist + (p.e0 + k) / p.ns * (p.n_bins + 2) + histogram_bin(p, n, nq, k), 1.0);
+  } else {
+    __shared__ int counts[kHistBins];
+    const int64_t k0 = (int64_t)blockIdx.x * (256 * p.per);
+    const int64_t k1 = k0 + 256 * p.per < p.E ? k0 + 256 * p.per : p.E;
+    const int64_t s = (p.e0 + k0) / p.ns;
+    const bool local = p.n_bins + 2 <= kHistBins && s == (p.e0 + k1 - 1) / p.ns;
+    if (local) {
+      for (int i = threadIdx.x; i < p.n_bins + 2; i += 256) counts[i] = 0;
+      __syncthreads();
+    }
+    for (int64_t k = k0 + threadIdx.x; k < k1; k += 256) {
+      const int64_t b = histogram_bin(p, n, nq, k);
+      if (local)
+        atomicAdd(&counts[b], 1);
+      else
+        atomicAdd(hist + (p.e0 + k) / p.ns * (p.n_bins + 2) + b, 1.0);
+    }
+    if (!local) return;
     __syncthreads();
+    for (int i = threadIdx.x; i < p.n_bins + 2; i += 256)
+      if (counts[i] != 0) atomicAdd(hist + s * (p.n_bins + 2) + i, (double)counts[i]);
   }
-  for (int64_t k = k0 + threadIdx.x; k < k1; k += 256) {
-    const int64_t b = histogram_bin(p, n, nq, k);
-    if (local)
-      atomicAdd(&counts[b], 1);
-    else
-      atomicAdd(hist + (p.e0 + k) / p.ns * (p.n_bins + 2) + b, 1.0);
-  }
-  if (!local) return;
-  __syncthreads();
-  for (int i = threadIdx.x; i < p.n_bins + 2; i += 256)
-    if (counts[i] != 0) atomicAdd(hist + s * (p.n_bins + 2) + i, (double)counts[i]);
 }
 
 // Mean over sub-ensembles of scale * acc[s][v] / samples_per_sub and sigma_T =
@@ -1678,8 +1684,15 @@ mp_status histogram_launch(int64_t E, const double* n, const double* nq, int32_t
   p.n_bins = n_bins;
   p.o_min = o_min;
   p.inv_width = 1.0 / width;
-  p.per = (int)(E / 65536 < 1 ? 1 : (E / 65536 > 8 ? 8 : E / 65536));
-  hipLaunchKernelGGL(histogram_kernel,
+  // Samples per thread, as E leaves some 256 workgroups.  Short sub-ensembles take one: few
+  // workgroups would lie in one, and the atomics are spread over as many histograms (1e5
+  // samples, 200 bins, by a sample each and by workgroup: 8.5 and 11 us at 100 samples a
+  // sub-ensemble, 11.0 and 9.6 at 1000; 1e6 samples: 41 and 55 at 500, 63 and 44 at 3000).  So do
+  // bins that do not fit where a thread has one sample anyway
+  p.per = E < 2 * 65536 ? 1 : (E >= 8 * 65536 ? 8 : (int)(E / 65536));
+  const bool one = ns < 768 || ns < 256 * p.per || (p.per == 1 && (int64_t)n_bins + 2 > kHistBins);
+  if (one) p.per = 1;
+  hipLaunchKernelGGL((one ? histogram_kernel<true> : histogram_kernel<false>),
                      dim3((unsigned)((E + 256 * p.per - 1) / (256 * p.per))), dim3(256), 0, stream, p,
                      n, nq, hist);
   MP_HIP_LAUNCH_CHECK("mp_observable_histogram launch");
