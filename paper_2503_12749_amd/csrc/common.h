@@ -143,6 +143,15 @@ __host__ __device__ inline const char* touch_word(const void* p, int64_t bytes, 
   return q + 4 <= (const char*)p + bytes ? q : nullptr;
 }
 
+// A grid of `blocks` workgroups in two dimensions, each with its number in wide_block();
+// those past the last have to end by themselves.  A launch counts its threads along a
+// dimension in 32 bits: beyond 2^32 it runs only what is left of them, without an error.
+inline dim3 wide_grid(int64_t blocks) {
+  const int64_t x = blocks < (1 << 22) ? blocks : 1 << 22;  // of at most 512 threads
+  return dim3((unsigned)x, (unsigned)((blocks + x - 1) / x));
+}
+__device__ inline int64_t wide_block() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
+
 // v of the lane that the DPP control names, for both halves of a double.
 template <int CTRL>
 __device__ inline double dpp_f64(double v) {

@@ -439,7 +439,7 @@ __global__ __launch_bounds__(64 * kSampleWaves) void sample_kernel(
   __shared__ PairCoef<F64> coef[PB];
   __shared__ double n_sum[kSampleWaves][kSampleMax];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t k0 = ((int64_t)blockIdx.x * kSampleWaves + wave) * per_wave;
+  const int64_t k0 = (wide_block() * kSampleWaves + wave) * per_wave;
   const int64_t left = E - k0;
   const int nk = left < per_wave ? (left < 0 ? 0 : (int)left) : per_wave;
   const int pairs = (int)(ldm / 2);
@@ -496,7 +496,7 @@ __global__ __launch_bounds__(256) void sample_small(int M, int64_t ldm, int64_t 
                                                     double* __restrict__ n_out) {
   constexpr bool F64 = PREC == MP_FP64;
   const int lane = threadIdx.x & 63, p = lane & (lps - 1);
-  const int64_t k = (((int64_t)blockIdx.x * 256 + threadIdx.x) / lps);
+  const int64_t k = (wide_block() * 256 + threadIdx.x) / lps;
   const bool valid = k < E;
   const PairCoef<F64> cf = pair_coef<F64>(r, p, M);
   double n = 0.0;
@@ -566,11 +566,11 @@ static mp_status sample_go(int32_t M, int64_t g0, int64_t E, const double* r, ui
     return MP_ERR_UNSUPPORTED;
   }
   if (M <= kSmallModes)
-    hipLaunchKernelGGL(sample_small<PREC>, dim3((unsigned)blocks), dim3(256), 0, stream, M, ldm, g0,
+    hipLaunchKernelGGL(sample_small<PREC>, wide_grid(blocks), dim3(256), 0, stream, M, ldm, g0,
                        E, (int)lps, r, seed, net, ab, n_out);
   else
-    hipLaunchKernelGGL(sample_kernel<PREC>, dim3((unsigned)blocks), dim3(64 * kSampleWaves), 0,
-                       stream, M, ldm, g0, E, (int)per_wave, r, seed, net, ab, n_out);
+    hipLaunchKernelGGL(sample_kernel<PREC>, wide_grid(blocks), dim3(64 * kSampleWaves), 0, stream, M,
+                       ldm, g0, E, (int)per_wave, r, seed, net, ab, n_out);
   MP_HIP_LAUNCH_CHECK("mp_sample launch");
   return MP_OK;
 }
