@@ -287,7 +287,9 @@ __global__ __launch_bounds__(kMlpThreads) void mlp_rows(MlpNet p, const uint16_t
   const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lh = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int group = wave / kMlpParts, pq = wave % kMlpParts;
-  const int row0 = blockIdx.x * kMlpRows;
+  const int64_t first = wide_block() * kMlpRows;
+  if (first >= p.batch) return;
+  const int row0 = (int)first;
   const int plane = kMlpRows * p.pitch;
   float* sums = (float*)(planes + 3 * plane);
   // elementwise work: row m of the block, columns pass + n8 .. + 7
@@ -466,7 +468,7 @@ __global__ __launch_bounds__(kMlpThreads) void mlp_rows(MlpNet p, const uint16_t
     double t = 0.0;
 #pragma unroll
     for (int w = 0; w < kMlpWaves; ++w) t += red[w];
-    part[blockIdx.x] = t;
+    part[wide_block()] = t;
   }
 }
 
@@ -690,8 +692,8 @@ mp_status mlp_loss_grad(const mp_mlp_shape* s, const uint16_t* w16, const float*
   if (r != MP_OK) return r;
   // one double per workgroup: fits the 2 batch wmax + 384 floats that follow the layers
   double* part = (double*)(((uintptr_t)((float*)ws + used) + 7) & ~(uintptr_t)7);
-  const int n_part = (batch + kMlpRows - 1) / kMlpRows;
-  hipLaunchKernelGGL(mlp_rows, dim3((unsigned)n_part), dim3(kMlpThreads), lds, st, p, w16, params, X,
+  const int n_part = (int)(((int64_t)batch + kMlpRows - 1) / kMlpRows);
+  hipLaunchKernelGGL(mlp_rows, wide_grid(n_part), dim3(kMlpThreads), lds, st, p, w16, params, X,
                      Y, (float*)ws, part);
   MlpTiles t{};
   for (int l = 0; l < p.L; ++l)
