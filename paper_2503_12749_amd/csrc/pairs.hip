@@ -203,6 +203,10 @@ __global__ __launch_bounds__(256, 1) void pair_corr_f32(PairParams p, const floa
         const int r = (int)(k1 - kb) + e / PT;
         lds[st][0][r][e % PT] = 0.f;
         lds[st][1][r][e % PT] = 0.f;
+        if (diag) continue;
+        // of both factors: 0 times an infinite last sample would be NaN
+        lds[st][2][r][e % PT] = 0.f;
+        lds[st][3][r][e % PT] = 0.f;
       }
       __syncthreads();
     }
