@@ -304,7 +304,9 @@ static_assert(PT == cmfma::kTile && PK == cmfma::kSlab, "tile shape of the share
 // box.  Bound by the FP32 matrix cores (72 % busy), then by the staging between
 // their products.  1e5 samples on 128^3 points, two full boxes, per term: 14.5 ms
 // before, 14.4 with the block test alone, 10.1 with the loads ahead as well,
-// 8.2 with the order of sum_item.
+// 8.2 with the order of sum_item.  D = 4 spills 51 registers around the loads and gains all the
+// same: counts of 2e4 samples on 48^4 points 41.7 ms before, 35.4 now; 2000 on 32^4
+// 1.41 and 0.78 ms.
 template <int D>
 __global__ __launch_bounds__(256, 2) void jointd_sum_f32(JointDParams p, int tau,
                                                         const float* __restrict__ tables,
@@ -942,17 +944,15 @@ mp_status jointd_launch(int32_t M, int64_t E, const void* C, const double* n, mp
   int kp_max = 0;
   for (int b = 0; b < d; ++b) kp_max = p.Kp[b] > kp_max ? p.Kp[b] : kp_max;
   const dim3 fgrid((unsigned)((E * kp_max + 255) / 256), (unsigned)(2 * d));
+  const mp_status sb = record_bands_launch(rec, E, d, K, kJD, band, stream);
+  if (sb != MP_OK) return sb;
   if (prec == MP_FP64) {
-    const mp_status sb = record_bands_launch(rec, E, d, K, kJD, band, stream);
-    if (sb != MP_OK) return sb;
     hipLaunchKernelGGL(jointd_factors<double>, fgrid, dim3(256), 0, stream, p, rec, band,
                        (double*)tables);
     for (int tau = 0; tau < 2; ++tau)
       hipLaunchKernelGGL(jointd_sum_f64, dim3((unsigned)items), dim3(256), 0, stream, p, tau,
                          (const double*)tables, band, acc);
   } else {
-    const mp_status sb = record_bands_launch(rec, E, d, K, kJD, band, stream);
-    if (sb != MP_OK) return sb;
     hipLaunchKernelGGL(jointd_factors<float>, fgrid, dim3(256), 0, stream, p, rec, band,
                        (float*)tables);
     for (int tau = 0; tau < 2; ++tau)

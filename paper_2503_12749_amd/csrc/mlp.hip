@@ -179,7 +179,8 @@ __global__ __launch_bounds__(MLP_THREADS) void mlp_layer(const float* __restrict
 // and its scattered stores 4000; a launch per layer and pass over 64 x 64 tiles,
 // each staging both operands through LDS element by element, took 31 us per forward
 // and 26 us per backward 256 x 256 layer at batch 256 (all seven products of a
-// training step take 38 us now).
+// training step take 38 us now).  The sums of four passes (widths up to 1024) do not all
+// fit: 31 of 256 registers spill.
 constexpr int kMlpRows = 16, kMlpWaves = 8, kMlpThreads = 64 * kMlpWaves;
 constexpr int kMlpGroup = 128, kMlpParts = 4, kMlpPass = 256;
 constexpr int kMlpPasses = 1024 / kMlpPass;                   // widths are at most 1024
@@ -596,14 +597,14 @@ static int64_t layer_offset(const mp_mlp_shape* s, int l) {
 
 int64_t mlp_param_count(const mp_mlp_shape* s) { return layer_offset(s, s->n_layers); }
 
-constexpr int kMseBlocks = 64;
+static int64_t mlp_parts(int32_t batch) { return ((int64_t)batch + kMlpRows - 1) / kMlpRows; }
+
 static int64_t act_elems(const mp_mlp_shape* s, int32_t batch) {
-  // Z and A of every layer (Z becomes dZ in the backward pass), two rows of the
-  // widest layer per sample (their start holds the loss partials), and padding
-  int64_t e = 0, wmax = 0;
+  // Z and A of every layer (Z becomes dZ in the backward pass), the loss partials (a double
+  // per workgroup of mlp_rows) and their alignment
+  int64_t e = 2 * mlp_parts(batch) + 2;
   for (int l = 0; l < s->n_layers; ++l) e += 2 * (int64_t)batch * s->width[l + 1];
-  for (int l = 0; l <= s->n_layers; ++l) wmax = wmax > s->width[l] ? wmax : s->width[l];
-  return e + 2 * (int64_t)batch * wmax + 2 * kMseBlocks + 256;
+  return e;
 }
 
 size_t mlp_workspace(const mp_mlp_shape* s, int32_t batch) {
@@ -690,9 +691,8 @@ mp_status mlp_loss_grad(const mp_mlp_shape* s, const uint16_t* w16, const float*
   const size_t lds = mlp_net(s, batch, p, &used);
   const mp_status r = mlp_lds((const void*)mlp_rows, lds);
   if (r != MP_OK) return r;
-  // one double per workgroup: fits the 2 batch wmax + 384 floats that follow the layers
   double* part = (double*)(((uintptr_t)((float*)ws + used) + 7) & ~(uintptr_t)7);
-  const int n_part = (int)(((int64_t)batch + kMlpRows - 1) / kMlpRows);
+  const int n_part = (int)mlp_parts(batch);
   hipLaunchKernelGGL(mlp_rows, wide_grid(n_part), dim3(kMlpThreads), lds, st, p, w16, params, X,
                      Y, (float*)ws, part);
   MlpTiles t{};

@@ -498,7 +498,7 @@ __device__ __attribute__((always_inline)) inline void fused_epilogue(
 // of the store of C.
 // NJ: 32-column blocks per wave.  4: the 256 x 256 tile; 2: a 256 x 128 tile
 // (fused: 128 modes x 64 samples) whose B planes use their first 128 rows,
-// for batched plans (a tile-shape candidate of the plan's autotuner).  Every
+// for products that it ends sooner (narrow_tiles; plans time both).  Every
 // output element goes through the same MFMA sequence in either shape, so the
 // results are the same bits.
 template <typename H, bool FUSED, bool PF, int NJ = 4>
@@ -2108,10 +2108,9 @@ size_t propagate_workspace(int32_t M, mp_precision prec) {
 }
 
 // Modes that a GEMM multiplies through: M rounded up to a pair of 32-deep slabs (the
-// FP8 product's depth; 16 for the FP64 kernel), not the whole padded row: the rest
-// of it is zeros, whose products leave every accumulator as it is.  Half of the
-// slabs at M = 16 .. 64, 1000 of 1024 modes at most at M = 1000 (none there), 8000
-// of 8064 at M = 8000.
+// FP8 product's depth; one of 16 for the FP64 kernel), not the whole padded row: the rest
+// of it is zeros, whose products leave every accumulator as it is.  64 of 128 modes up to
+// M = 64 (FP64: 16 of 128 up to M = 16), 8000 of 8064 at M = 8000, all 1024 at M = 1000.
 int k_modes(int32_t M, int depth) { return (M + depth - 1) / depth * depth; }
 
 static int grid_tiles(int64_t ldm, int64_t ncols, int bm, int bn) {
@@ -2183,6 +2182,7 @@ mp_status pack_launch(int32_t M, const double* T, mp_precision prec, void* packe
 // turn each (M = 900, 1e3 samples): FP32 125 and 225 us, split FP16 44 and 63 us; three
 // against two (M = 436, 1e4): 196 and 239, 78 and 81 us; two against one (M = 300,
 // 7e3): 86 us wide in FP32, 36 us in split FP16, narrow slower.  Both give the same bits.
+// The one-sided and FP8-corrected kernels have the 256 x 256 tile only.
 static bool narrow_tiles(int64_t ldm, int64_t ncols) {
   const int64_t rows = 2 * ldm / S_BM;
   const int64_t wide = (rows * ((ncols + 255) / 256) + kCus - 1) / kCus;

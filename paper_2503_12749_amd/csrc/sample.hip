@@ -15,8 +15,8 @@
 //
 // A wavefront takes its samples one or two at a time: lanes stride over mode
 // pairs, so each sample's column (contiguous over modes) is written with
-// coalesced stores, and n = alpha . beta is reduced across the wave with
-// shuffles.  Networks of at most 64 modes share a wave between several samples.  The FP64
+// coalesced stores, and n = alpha . beta is summed over the wave at its
+// end.  Networks of at most 64 modes share a wave between several samples.  The FP64
 // path evaluates Box-Muller with the library's FP64 log and sincos; the FP32
 // and split paths evaluate it by short FP64 series and round the radius and
 // the angle's sine and cosine to FP32 once (no systematic error beyond that
